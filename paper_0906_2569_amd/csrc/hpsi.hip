@@ -25,29 +25,20 @@
 
 #include "fft_reg.h"
 #include "plan.h"
+#include "plane_wave.h"
 #include "profile.h"
+#include "zpass.h"
 
 namespace {
+
+using pw::ZFns;
+using pw::gamma_pack;
+using pw::to_t;
+using pw::z_tile;
 
 constexpr int ZSB = 16;        // sticks per workgroup in the z passes
 constexpr int ZTHREADS = 128;
 constexpr int PTHREADS = 256;
-
-template <typename T>
-__device__ __forceinline__ cpx<T> to_t(c128 v) { return cpx<T>{(T)v.x, (T)v.y}; }
-
-// Workgroup -> (stick chunk, band) of the z passes.  Workgroups go to the 8
-// XCDs round-robin by linear id, so all chunks of one band get ids of one
-// residue mod 8: each band's scattered sphere reads then meet one L2.  The
-// grid has gz * roundup(nb, 8) workgroups; those past the last band exit.
-constexpr int kXcds = 8;
-__device__ __forceinline__ bool z_tile(int gz, int nb, int& chunk, int& band) {
-  const int id = blockIdx.x;
-  const int slot = id / kXcds;
-  band = (slot / gz) * kXcds + id % kXcds;
-  chunk = slot % gz;
-  return band < nb;
-}
 
 // ---------------------------------------------------------------------------
 // pass 1: sphere -> sticks, inverse z transform
@@ -764,14 +755,6 @@ k_zfwd_grp(SphereMap m, const cpx<T>* __restrict__ sticks, const c128* __restric
 // transform f(G) = (V psi_a)(G) + i (V psi_b)(G), and the gather separates
 // (V psi_a)(G) = (f(G) + conj f(-G)) / 2, (V psi_b)(G) = (f(G) - conj f(-G)) / 2i.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ c128 gamma_pack(const c128* __restrict__ pa, const c128* __restrict__ pb, int enc) {
-  const int g = enc >> 1;
-  c128 a = pa[g];
-  c128 b = pb ? pb[g] : c128{0.0, 0.0};
-  if (g == 0) { a.y = 0.0; b.y = 0.0; }   // psi(0) is real
-  return (enc & 1) ? c128{a.x + b.y, b.x - a.y} : c128{a.x - b.y, a.y + b.x};
-}
-
 template <typename T, int LS>
 __global__ void __launch_bounds__(ZRTHREADS)
 k_zinv_reg_g(SphereMap m, const c128* __restrict__ psi, int ldpsi, cpx<T>* __restrict__ sticks,
@@ -957,56 +940,45 @@ k_zfwd_grp_g(SphereMap m, cpx<T>* __restrict__ sticks, const cpx<T>* __restrict_
   for (int j = 0; j < LS; ++j) io[(size_t)(g + G * j) * m.ldst] = x[j];
 }
 
-template <typename T>
-struct ZGrpFns {
-  void (*inv)(SphereMap, const c128*, int, cpx<T>*, const cpx<T>*, int, int) = nullptr;
-  void (*fwd)(SphereMap, const cpx<T>*, const c128*, int, c128*, int, const cpx<T>*, double, int, int, int) = nullptr;
-  void (*inv_g)(SphereMap, const c128*, int, cpx<T>*, const cpx<T>*, int, int, int) = nullptr;
-  void (*fwd_g)(SphereMap, cpx<T>*, const cpx<T>*, int, int) = nullptr;
-};
 template <typename T, int LS>
-ZGrpFns<T> zgrp_set() {
-  ZGrpFns<T> f;
+ZFns<T> zgrp_set() {
+  ZFns<T> f;
   f.inv = k_zinv_grp<T, LS>;
   f.fwd = k_zfwd_grp<T, LS>;
   f.inv_g = k_zinv_grp_g<T, LS>;
   f.fwd_g = k_zfwd_grp_g<T, LS>;
+  f.sticks = ZGSTICKS;
+  f.threads = ZGTHREADS;
   return f;
 }
 
 // 16-lane-group z passes for n3 = 16 LS, or none
 template <typename T>
-ZGrpFns<T> zgrp_kernels(int n3) {
+ZFns<T> zgrp_kernels(int n3) {
   switch (n3) {
     case 80: return zgrp_set<T, 5>();
     case 96: return zgrp_set<T, 6>();
     case 128: return zgrp_set<T, 8>();
     case 144: return zgrp_set<T, 9>();
-    default: return ZGrpFns<T>{};
+    default: return ZFns<T>{};
   }
 }
 
-template <typename T>
-struct ZRegFns {
-  void (*inv)(SphereMap, const c128*, int, cpx<T>*, const cpx<T>*, int, int) = nullptr;
-  void (*fwd)(SphereMap, const cpx<T>*, const c128*, int, c128*, int, const cpx<T>*, double, int, int, int) = nullptr;
-  void (*inv_g)(SphereMap, const c128*, int, cpx<T>*, const cpx<T>*, int, int, int) = nullptr;
-  void (*fwd_g)(SphereMap, cpx<T>*, const cpx<T>*, int, int) = nullptr;
-};
-
 template <typename T, int LS>
-ZRegFns<T> zreg_pair() {
-  ZRegFns<T> f;
+ZFns<T> zreg_pair() {
+  ZFns<T> f;
   f.inv = k_zinv_reg<T, LS>;
   f.fwd = k_zfwd_reg<T, LS>;
   f.inv_g = k_zinv_reg_g<T, LS>;
   f.fwd_g = k_zfwd_reg_g<T, LS>;
+  f.sticks = ZRSTICKS;
+  f.threads = ZRTHREADS;
   return f;
 }
 
 // register-resident z passes for n3 = 4 LS (same lengths as the plane pass)
 template <typename T>
-ZRegFns<T> zreg_kernels(int n3) {
+ZFns<T> zreg_kernels(int n3) {
   if (n3 % 4 != 0) return {};
   const bool f64 = sizeof(T) == 8;
   switch (n3 / 4) {
@@ -1017,15 +989,27 @@ ZRegFns<T> zreg_kernels(int n3) {
     case 15: return zreg_pair<T, 15>();
     case 16: return zreg_pair<T, 16>();
     case 18: return zreg_pair<T, 18>();
-    case 20: return f64 ? ZRegFns<T>{} : zreg_pair<T, 20>();
-    case 24: return f64 ? ZRegFns<T>{} : zreg_pair<T, 24>();
-    case 25: return f64 ? ZRegFns<T>{} : zreg_pair<T, 25>();
-    case 27: return f64 ? ZRegFns<T>{} : zreg_pair<T, 27>();
-    case 30: return f64 ? ZRegFns<T>{} : zreg_pair<T, 30>();
-    case 32: return f64 ? ZRegFns<T>{} : zreg_pair<T, 32>();
-    case 36: return f64 ? ZRegFns<T>{} : zreg_pair<T, 36>();
+    case 20: return f64 ? ZFns<T>{} : zreg_pair<T, 20>();
+    case 24: return f64 ? ZFns<T>{} : zreg_pair<T, 24>();
+    case 25: return f64 ? ZFns<T>{} : zreg_pair<T, 25>();
+    case 27: return f64 ? ZFns<T>{} : zreg_pair<T, 27>();
+    case 30: return f64 ? ZFns<T>{} : zreg_pair<T, 30>();
+    case 32: return f64 ? ZFns<T>{} : zreg_pair<T, 32>();
+    case 36: return f64 ? ZFns<T>{} : zreg_pair<T, 36>();
     default: return {};
   }
+}
+
+// z passes of the length: the quad form where a quad holds a column in
+// registers, else the 16-lane form, else (float64) the two-step form; inv ==
+// nullptr: the LDS Stockham kernels
+template <typename T>
+ZFns<T> z_fns(int n3) {
+  ZFns<T> f = zreg_kernels<T>(n3);
+  if (f.inv == nullptr) f = zgrp_kernels<T>(n3);
+  if constexpr (sizeof(T) == 8)
+    if (f.inv == nullptr) f = pw::zwave_f64(n3);
+  return f;
 }
 
 // ---------------------------------------------------------------------------
@@ -1074,6 +1058,48 @@ int plane_batch(int n1, int n2, int nxr) {
   return 0;
 }
 
+// The two-step kernel of the LDS form, or none where no kernel covers the
+// grid or one plane with two waves does not fit.
+constexpr size_t kPlaneWaveMaxLds = 160 * 1024;
+constexpr int kCus = 256;
+template <typename T>
+pw::PlaneWave<T> plane_wave_of(int n1, int n2, int nxr) {
+  if constexpr (sizeof(T) == 8) {
+    const pw::PlaneWave<T> e = pw::plane_wave_f64(n1, n2);
+    if (e.fn != nullptr && e.lds(nxr, 1, 2) <= kPlaneWaveMaxLds) return e;
+  }
+  return {};
+}
+
+// z planes and waves per workgroup (pp_only = 1: one plane): the pair that
+// keeps the most waves of a CU at work.  A workgroup takes the three phases
+// in rounds of nwaves x cols columns (rows); a CU holds as many workgroups as
+// fit its LDS and the waves its registers allow; below 16 waves the latency
+// of one is less and less hidden by the others.
+template <typename T>
+pw::PlaneWaveShape plane_wave_shape(const pw::PlaneWave<T>& e, int n2, int nxr, int pp_only) {
+  pw::PlaneWaveShape best;
+  double score = -1.0;
+  for (int pp = 1; pp <= (pp_only ? 1 : 6); ++pp)
+    for (int nw = 1; nw <= e.max_waves; ++nw) {
+      const size_t lds = e.lds(nxr, pp, nw);
+      if (lds > kPlaneWaveMaxLds) continue;
+      const int wgs = std::min((int)(kPlaneWaveMaxLds / lds), e.max_waves / nw);
+      if (wgs < 1) continue;
+      const double cy = ceil_div(pp * nxr, e.cols), rx = ceil_div(pp * n2, e.rows);   // rounds of one wave
+      const double work = 2.0 * pp * nxr / e.cols + 2.0 * pp * n2 / e.rows;
+      const double time = 2.0 * std::ceil(cy / nw) + 2.0 * std::ceil(rx / nw);
+      const double util = work / (nw * time);
+      const double s = pp_only ? 1.0 / time + 1e-3 * util : util * std::sqrt(std::min(1.0, wgs * nw / 16.0));
+      if (s > score * 1.02) {
+        score = s;
+        best.pp = pp;
+        best.nwaves = nw;
+      }
+    }
+  return best;
+}
+
 // Forms of the plane pass (pw_plan_info reports them).
 enum PlaneForm { kFormQuad = 0, kFormSplit = 1, kFormGroup = 2, kFormLds = 3 };
 
@@ -1082,7 +1108,7 @@ bool plane_form_ok(int form, int n1, int n2, int nxr) {
   switch (form) {
     case kFormQuad: return plane_quad_fits<T>(n1, n2, nxr);
     case kFormGroup: return plane_oct_fits<T>(n1, n2, nxr);
-    case kFormLds: return plane_batch<T>(n1, n2, nxr) > 0;
+    case kFormLds: return plane_wave_of<T>(n1, n2, nxr).fn != nullptr || plane_batch<T>(n1, n2, nxr) > 0;
     default: return true;   // three kernels fit any grid the plan accepts
   }
 }
@@ -1100,6 +1126,13 @@ int plane_form_for(int mode, int n1, int n2, int nxr) {
   if (mode == 1) return kFormSplit;
   if (mode == 2 && plane_form_ok<T>(kFormGroup, n1, n2, nxr)) return kFormGroup;
   if (mode == 4 && plane_form_ok<T>(kFormQuad, n1, n2, nxr)) return kFormQuad;
+  // float64 planes on which the two-step kernel of the LDS form was measured
+  // faster than the register kernel (64^2 69 against 108 us, 72^2 107 against
+  // 129); at 32^2 to 48^2 (76..136 us) the register kernel is level or faster
+  // (74..93), at 60^2 it is level alone (114 against 109) and faster beside
+  // the projector products (269 against 287 us a product of 100 bands), at
+  // 80^2 to 128^2 (118..138) the lane-group kernel is faster (107..136)
+  if (n1 == n2 && n1 >= 64 && n1 <= 72 && plane_wave_of<T>(n1, n2, nxr).fn != nullptr) return kFormLds;
   if (plane_reg_kernel<T, 2>(n1, n2) != nullptr && plane_reg_lds_bytes<T>(n1, nxr, 2) <= kPlaneRegMaxLds)
     return kFormQuad;
   for (int f : {(int)kFormGroup, (int)kFormQuad, (int)kFormLds})
@@ -1502,9 +1535,8 @@ pw_status pw::plan_create(pw_ctx ctx, const pw_problem* pr, const pw_plan_opts* 
   PLAN_TRY(upload(p, &p->i1_hx, i1_hx));
   PLAN_TRY(upload(p, &p->zidx, zidx));
   PLAN_TRY(upload(p, &p->col_ptr, col_ptr));
-  // the (column, y) -> stick map of the lane-group kernel: built for every
-  // plan whose grid that kernel covers (plane_mode 3 may pick it later)
-  if (plane_oct_kernel<double>(n1, n2) != nullptr) {
+  // the (column, y) -> stick map of the lane-group and two-step kernels
+  {
     std::vector<int> cy_st((size_t)nxr * n2, -1);
     for (size_t s2 = 0; s2 < st_hx.size(); ++s2) cy_st[(size_t)st_hx[s2] * n2 + st_i2[s2]] = (int)s2;
     PLAN_TRY(upload(p, &p->cy_st, cy_st));
@@ -1692,6 +1724,7 @@ struct PlaneLaunch {
   size_t plds = 0;
   PlaneOctFn<T> poct = nullptr;   // lane-group kernel
   size_t olds = 0;
+  pw::PlaneWave<T> pwv;           // LDS form on two-step transforms, where it covers the grid ...
   int cb = 0;                     // generic LDS kernel: transforms per batch
   size_t pl = 0;                  // its LDS (or that of the three-kernel form)
 };
@@ -1724,6 +1757,11 @@ pw_status plane_setup(pw_plan p, int form, PlaneLaunch<T>& L) {
       if (L.olds > 64 * 1024) PW_TRY(raise_lds_limit((const void*)L.poct, (int)L.olds));
       break;
     case kFormLds:
+      L.pwv = plane_wave_of<T>(n1, n2, nxr);
+      if (L.pwv.fn != nullptr) {
+        PW_TRY(raise_lds_limit((const void*)L.pwv.fn, (int)kPlaneWaveMaxLds));
+        break;
+      }
       L.cb = plane_batch<T>(n1, n2, nxr);
       PW_CHECK(L.cb > 0, PW_EINVAL, "grid too large for the generic plane kernel");
       L.pl = plane_lds_bytes<T>(n1, n2, nxr, L.cb);
@@ -1750,6 +1788,14 @@ void plane_launch(pw_plan p, const PlaneLaunch<T>& L, cpx<T>* st, const T* vr, c
       L.poct<<<dim3(nbc, p->n3), OctCfg<T>::threads, L.olds, s>>>(m, st, vr, tw1);
       break;
     case kFormLds:
+      if (L.pwv.fn != nullptr) {
+        // full workgroups only where there are enough of them
+        pw::PlaneWaveShape sh = plane_wave_shape<T>(L.pwv, p->n2, p->nxr, 0);
+        if ((long)nbc * ceil_div(p->n3, sh.pp) < 2 * kCus) sh = plane_wave_shape<T>(L.pwv, p->n2, p->nxr, 1);
+        const size_t lds = L.pwv.lds(p->nxr, sh.pp, sh.nwaves);
+        L.pwv.fn<<<dim3(nbc, ceil_div(p->n3, sh.pp)), 64 * sh.nwaves, lds, s>>>(m, st, vr, tw1, tw2, sh.pp);
+        break;
+      }
       k_plane<T><<<dim3(nbc, p->n3), PTHREADS, L.pl, s>>>(m, st, vr, tw1, tw2, L.cb);
       break;
     default: {
@@ -1845,11 +1891,8 @@ pw_status hpsi_fft(pw_plan p, int nb, const c128* psi, int ldpsi, c128* hpsi, in
   const size_t zl = z_lds_bytes<T>(p->n3);
   cpx<T>* st = static_cast<cpx<T>*>(p->sticks);
   const int gz = ceil_div(p->nst, ZSB);
-  const ZRegFns<T> zr = p->use_reg_plane ? zreg_kernels<T>(p->n3) : ZRegFns<T>{};
-  const int gzr = ceil_div(p->nst, ZRSTICKS);
-  // 16-lane-group z passes where no quad form exists (the complex path)
-  const ZGrpFns<T> zg = (p->use_reg_plane && zr.inv == nullptr) ? zgrp_kernels<T>(p->n3) : ZGrpFns<T>{};
-  const int gzg = ceil_div(p->nst, ZGSTICKS);
+  const ZFns<T> zr = z_fns<T>(p->n3);
+  const int gzr = zr.inv ? ceil_div(p->nst, zr.sticks) : 0;
   // algorithmic bytes per band: sphere in/out (complex128) and one write plus
   // one read of the stick columns per transform direction; V(r) once per pass
   const double sphere_b = 16.0 * p->npw, stick_b = (double)sizeof(cpx<T>) * p->n3 * p->nst;
@@ -1865,17 +1908,13 @@ pw_status hpsi_fft(pw_plan p, int nb, const c128* psi, int ldpsi, c128* hpsi, in
     if (gam) {
       pw::ProfScope ps(pw::PK_ZINV, s, nbb * sphere_b + nbc * stick_b);
       if (zr.inv_g)
-        zr.inv_g<<<zrgrid, ZRTHREADS, 0, s>>>(m, psi + (size_t)b0 * ldpsi, ldpsi, st, tw3, gzr, nbc, nbb);
-      else if (zg.inv_g)
-        zg.inv_g<<<gzg * nbc8, ZGTHREADS, 0, s>>>(m, psi + (size_t)b0 * ldpsi, ldpsi, st, tw3, gzg, nbc, nbb);
+        zr.inv_g<<<zrgrid, zr.threads, 0, s>>>(m, psi + (size_t)b0 * ldpsi, ldpsi, st, tw3, gzr, nbc, nbb);
       else
         k_zinv_g<T><<<zgrid, ZTHREADS, zl, s>>>(m, psi + (size_t)b0 * ldpsi, ldpsi, st, tw3, gz, nbc, nbb);
     } else {
       pw::ProfScope ps(pw::PK_ZINV, s, nbc * (sphere_b + stick_b));
       if (zr.inv)
-        zr.inv<<<zrgrid, ZRTHREADS, 0, s>>>(m, psi + (size_t)c0 * ldpsi, ldpsi, st, tw3, gzr, nbc);
-      else if (zg.inv)
-        zg.inv<<<gzg * nbc8, ZGTHREADS, 0, s>>>(m, psi + (size_t)c0 * ldpsi, ldpsi, st, tw3, gzg, nbc);
+        zr.inv<<<zrgrid, zr.threads, 0, s>>>(m, psi + (size_t)c0 * ldpsi, ldpsi, st, tw3, gzr, nbc);
       else
         k_zinv<T><<<zgrid, ZTHREADS, zl, s>>>(m, psi + (size_t)c0 * ldpsi, ldpsi, st, tw3, gz, nbc);
     }
@@ -1886,9 +1925,7 @@ pw_status hpsi_fft(pw_plan p, int nb, const c128* psi, int ldpsi, c128* hpsi, in
     if (gam) {
       pw::ProfScope ps(pw::PK_ZFWD, s, nbb * sphere_b + nbc * stick_b);
       if (zr.fwd_g)
-        zr.fwd_g<<<zrgrid, ZRTHREADS, 0, s>>>(m, st, tw3, gzr, nbc);
-      else if (zg.fwd_g)
-        zg.fwd_g<<<gzg * nbc8, ZGTHREADS, 0, s>>>(m, st, tw3, gzg, nbc);
+        zr.fwd_g<<<zrgrid, zr.threads, 0, s>>>(m, st, tw3, gzr, nbc);
       else
         k_zfwd_g<T><<<zgrid, ZTHREADS, zl, s>>>(m, st, tw3, gz, nbc);
       if (join != nullptr && c0 == 0) PW_HIP(hipStreamWaitEvent(s, join, 0));
@@ -1904,13 +1941,9 @@ pw_status hpsi_fft(pw_plan p, int nb, const c128* psi, int ldpsi, c128* hpsi, in
     {
       pw::ProfScope ps(pw::PK_ZFWD, s, nbc * (sphere_b + stick_b));
       if (zr.fwd)
-        zr.fwd<<<zrgrid, ZRTHREADS, 0, s>>>(m, st, psi + (size_t)c0 * ldpsi, ldpsi,
+        zr.fwd<<<zrgrid, zr.threads, 0, s>>>(m, st, psi + (size_t)c0 * ldpsi, ldpsi,
                                             hpsi + (size_t)c0 * ldhpsi, ldhpsi, tw3,
                                             1.0 / (double)p->N, accumulate ? 3 : 0, gzr, nbc);
-      else if (zg.fwd)
-        zg.fwd<<<gzg * nbc8, ZGTHREADS, 0, s>>>(m, st, psi + (size_t)c0 * ldpsi, ldpsi,
-                                               hpsi + (size_t)c0 * ldhpsi, ldhpsi, tw3,
-                                               1.0 / (double)p->N, accumulate ? 3 : 0, gzg, nbc);
       else
         k_zfwd<T><<<zgrid, ZTHREADS, zl, s>>>(m, st, psi + (size_t)c0 * ldpsi, ldpsi,
                                                hpsi + (size_t)c0 * ldhpsi, ldhpsi, tw3,
@@ -1932,17 +1965,17 @@ pw_status pw::psi_to_rows(pw_plan p, int nt, int nbands, const c128* psi, int ld
   const cpx<double>* tw2 = (const cpx<double>*)p->tw64_2;
   const cpx<double>* tw3 = (const cpx<double>*)p->tw64_3;
   cpx<double>* st = static_cast<cpx<double>*>(p->sticks);
-  const ZRegFns<double> zr = p->use_reg_plane ? zreg_kernels<double>(p->n3) : ZRegFns<double>{};
+  const ZFns<double> zr = z_fns<double>(p->n3);
   const int nt8 = ceil_div(nt, 8) * 8;
-  const int gzr = ceil_div(p->nst, ZRSTICKS), gz = ceil_div(p->nst, ZSB);
+  const int gzr = zr.inv ? ceil_div(p->nst, zr.sticks) : 0, gz = ceil_div(p->nst, ZSB);
   const size_t zl = z_lds_bytes<double>(p->n3);
   if (p->gamma) {
     if (zr.inv_g)
-      zr.inv_g<<<gzr * nt8, ZRTHREADS, 0, s>>>(m, psi, ldpsi, st, tw3, gzr, nt, nbands);
+      zr.inv_g<<<gzr * nt8, zr.threads, 0, s>>>(m, psi, ldpsi, st, tw3, gzr, nt, nbands);
     else
       k_zinv_g<double><<<gz * nt8, ZTHREADS, zl, s>>>(m, psi, ldpsi, st, tw3, gz, nt, nbands);
   } else if (zr.inv) {
-    zr.inv<<<gzr * nt8, ZRTHREADS, 0, s>>>(m, psi, ldpsi, st, tw3, gzr, nt);
+    zr.inv<<<gzr * nt8, zr.threads, 0, s>>>(m, psi, ldpsi, st, tw3, gzr, nt);
   } else {
     k_zinv<double><<<gz * nt8, ZTHREADS, zl, s>>>(m, psi, ldpsi, st, tw3, gz, nt);
   }
@@ -2013,9 +2046,11 @@ bool nl_beside(pw_plan p, bool f64) {
   const int form = f64 ? p->form64 : p->form32;
   switch (form) {
     case kFormSplit: return false;
-    case kFormGroup:   // its workgroup holds more than 64 KB of LDS
+    case kFormGroup:
+      // beside while two workgroups fit a CU's LDS (float64 96^2, 72 KB: 4.53
+      // against 5.18 ms per product of 300 bands); at 144^2 (80 and 160 KB) after
       return (f64 ? plane_oct_lds_bytes<double>(p->n1, p->nxr) : plane_oct_lds_bytes<float>(p->n1, p->nxr)) <=
-             64 * 1024;
+             76 * 1024;
     case kFormQuad:
       return (f64 ? plane_reg_lds_bytes<double>(p->n1, p->nxr, 1) : plane_reg_lds_bytes<float>(p->n1, p->nxr, 1)) <=
              kPlaneRegMaxLds;

@@ -82,7 +82,6 @@ struct pw_plan_s {
   int nbeta = 0, nblk = 0, nhmax = 0;
   int ldb = 0;              // leading dimension of the plan's beta copies
   int band_chunk = 0;       // bands per FFT pass (stick workspace capacity)
-  bool use_reg_plane = true;  // register-resident z passes where the grid allows
   bool split64 = false, split32 = false;  // three-kernel plane pass (float64 / float32)
   int form64 = 0, form32 = 0;   // plane pass form per precision: 0 register (quad) kernel,
                                 // 1 three kernels, 2 lane-group kernel, 3 generic LDS kernel

@@ -1,0 +1,29 @@
+// Plane pass kernels on wave-local two-step transforms (plane_wave_impl.h):
+// lookup by grid size.
+#pragma once
+#include "plan.h"
+
+namespace pw {
+
+template <typename T>
+struct PlaneWave {
+  void (*fn)(SphereMap, cpx<T>*, const T*, const cpx<T>*, const cpx<T>*, int) = nullptr;
+  int ys = 0;           // LDS stride of an x column
+  int wave_words = 0;   // exchange words (of T) of a wave
+  int rows = 0, cols = 0;   // rows / x columns a wave transforms at a time
+  int max_waves = 0;        // per workgroup
+  size_t lds(int nxr, int pp, int nwaves) const {
+    return sizeof(cpx<T>) * (size_t)pp * (nxr + 2) * ys + sizeof(T) * (size_t)nwaves * wave_words;
+  }
+};
+
+// z planes per workgroup and waves of a launch
+struct PlaneWaveShape {
+  int pp = 0, nwaves = 0;
+};
+
+// fn == nullptr where no kernel covers n1 x n2
+PlaneWave<double> plane_wave_f64(int n1, int n2);
+PlaneWave<double> plane_wave_f64_pairs(int n1, int n2);   // n1 != n2
+
+}  // namespace pw
