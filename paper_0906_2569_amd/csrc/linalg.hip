@@ -911,7 +911,7 @@ __device__ __forceinline__ Refl householder(c128 al, double xn2) {
 template <int NC, int CRT, int CBW = CB>
 __global__ void __launch_bounds__(CT) k_tridiag_coop(int n, c128* __restrict__ A, int ld, double* __restrict__ d,
                                                      double* __restrict__ e, c128* __restrict__ tau,
-                                                     int* __restrict__ info, CoopBuf cb) {
+                                                     int* __restrict__ info, CoopBuf cb, int kstop) {
   constexpr int NW = CT / 64;             // waves
   constexpr int NH = CT / CBW;            // row groups (threads t and t + CBW share columns)
   constexpr int RH = CRT / NH;            // rows per thread
@@ -1171,8 +1171,218 @@ __global__ void __launch_bounds__(CT) k_tridiag_coop(int n, c128* __restrict__ A
 #pragma unroll
     for (int c = 0; c < NC; ++c) vk[c] = vk1[c];
     tk = h.tau;
+    if (k + 2 == kstop) {
+      // the rest goes to one workgroup: the block [kstop, n) with reflector
+      // kstop - 1 pending (row R of B is the conjugate of column R)
+#pragma unroll
+      for (int c = 0; c < NC; ++c)
+#pragma unroll
+        for (int i = 0; i < RH; ++i) {
+          const int R = row_of(half * RH + i);
+          if (ok[c] && jc[c] >= kstop && R >= kstop && R < n) A[(size_t)R * ld + jc[c]] = cconj(a[c][i]);
+        }
+      return;
+    }
     __syncthreads();
   }
+}
+
+// ---------------------------------------------------------------------------
+// Householder tridiagonalization of a trailing block of at most 96 rows in
+// the registers of one workgroup: 16 x TC threads, thread (tr, tc) holding
+// entries (tr + 16 p, tc + TC q) of the block, p < SR, q < SC.  `base` is the
+// block's first row; with `pending`, reflector base - 1 (stored in A and tau)
+// has still to be applied to it (the state k_tridiag_coop leaves).
+//
+// Per column c, with the reflector v, tau of column c - 1 not yet applied:
+//   1. the column sums of conj(a) v over the 16 lanes of a row group are A v,
+//      by Hermitian symmetry, with no sums across waves; R = v^H A v beside
+//      them (real, so -1/2 tau (p^H v) = -1/2 |tau|^2 R);
+//   2. barrier; w = tau A v - 1/2 |tau|^2 R v; column c is updated first, and
+//      its 16 lanes form its norm and the reflector of column c, which they
+//      publish; the updates of the other columns, A -= v w^H + w v^H, fill the
+//      latency of that chain;
+//   3. barrier; every thread reads its entries of the new reflector.
+// Two workgroup barriers and no memory round trip per column: the step is
+// bound by that latency chain (1.2 us a column at 48 rows, 2.0 at 96, where the
+// float64 FMAs of one CU, 12 per entry, add to it).  48 rows 308 -> 56 us and
+// 63 rows 400 -> 82 against k_tridiag, which goes through memory; 64 rows 239
+// -> 83 and 96 rows 385 -> 189 against the cooperative kernel (3.7 us a column).
+// At 128 rows the entries spill (558 us against 486): larger blocks hand
+// over at 96.
+// ---------------------------------------------------------------------------
+constexpr int kRegTridiagN = 96;
+
+// sum over the 16 lanes of a DPP row; every lane gets the same bits
+__device__ __forceinline__ double row_sum(double v) {
+  v += row_partner<0>(v);
+  v += row_partner<1>(v);
+  v += row_partner<2>(v);
+  v += row_partner<3>(v);
+  return v;
+}
+
+// 1 / sqrt(s) and 1 / x to float64 rounding from the hardware estimates (two
+// Newton steps): a much shorter dependent chain than the IEEE sequences
+__device__ __forceinline__ double newton_rsqrt(double s) {
+  double r = __builtin_amdgcn_rsq(s);
+  r = fma(0.5 * r, fma(-s * r, r, 1.0), r);
+  return fma(0.5 * r, fma(-s * r, r, 1.0), r);
+}
+__device__ __forceinline__ double newton_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+
+// householder() with the square root and the divisions through the above;
+// sums of squares out of their range take householder() itself
+__device__ __forceinline__ Refl householder_fast(c128 al, double xn2) {
+  const double s = al.x * al.x + al.y * al.y + xn2;
+  if (!(s > 1e-280 && s < 1e280)) return householder(al, xn2);
+  Refl r;
+  if (xn2 == 0.0 && al.y == 0.0) {
+    r.tau = c128{0.0, 0.0}; r.beta = al.x; r.scale = c128{0.0, 0.0};
+    return r;
+  }
+  const double q = newton_rsqrt(s), nrm0 = s * q;
+  const double nrm = fma(0.5 * q, fma(-nrm0, nrm0, s), nrm0);   // sqrt(s) to the last place
+  const double sg = al.x >= 0.0 ? -1.0 : 1.0;
+  const double beta = sg * nrm, ib = sg * q;
+  r.beta = beta;
+  r.tau = c128{(beta - al.x) * ib, -al.y * ib};
+  const c128 den = c128{al.x - beta, al.y};
+  const double id = newton_rcp(den.x * den.x + den.y * den.y);
+  r.scale = c128{den.x * id, -den.y * id};
+  return r;
+}
+
+template <int TC, int SR, int SC>
+__global__ void __launch_bounds__(16 * TC) k_tridiag_reg(int n, int base, int pending, c128* __restrict__ A, int ld,
+                                                         double* __restrict__ d, double* __restrict__ e,
+                                                         c128* __restrict__ tau, const int* __restrict__ info) {
+  if (*info != 0) return;
+  static_assert(16 * SR == TC * SC, "square block");
+  constexpr int M = 16 * SR, NW = TC / 4;
+  constexpr int V = SC <= 2 ? 4 : 8;   // column sums of a thread (re, then im), padded to a power of two
+  __shared__ c128 s_y[M], s_v[M], s_t;
+  __shared__ double s_r[NW];
+  const int m = n - base, tid = threadIdx.x, tr = tid & 15, tc = tid >> 4, lane = tid & 63;
+  c128 a[SR][SC], vr[SR], vc[SC], t{0.0, 0.0};
+#pragma unroll
+  for (int p = 0; p < SR; ++p)
+#pragma unroll
+    for (int q = 0; q < SC; ++q) {
+      const int i = tr + 16 * p, j = tc + TC * q;
+      a[p][q] = (i < m && j < m) ? A[(size_t)(base + j) * ld + base + i] : c128{0.0, 0.0};
+    }
+  // no reflector before the first column: v = 0 (the update below changes nothing)
+  const c128* v0 = A + (size_t)(base - pending) * ld + base;
+  if (pending) t = tau[base - 1];
+#pragma unroll
+  for (int p = 0; p < SR; ++p) vr[p] = (pending && tr + 16 * p < m) ? v0[tr + 16 * p] : c128{0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < SC; ++q) vc[q] = (pending && tc + TC * q < m) ? v0[tc + TC * q] : c128{0.0, 0.0};
+
+#pragma unroll
+  for (int qc = 0; qc < SC; ++qc) {
+    constexpr int rows_per = TC / 16;
+    const int p0 = qc * rows_per;   // rows below 16 p0 are done (compile-time after unrolling)
+    for (int cc = 0; cc < TC; ++cc) {
+      const int c = qc * TC + cc;
+      if (c >= m) return;   // uniform
+      // 1. A v and v^H A v (v is zero above row c)
+      double v[V], r = 0.0;
+#pragma unroll
+      for (int k = 0; k < V; ++k) v[k] = 0.0;
+#pragma unroll
+      for (int q = qc; q < SC; ++q) {
+        c128 u{0.0, 0.0};
+#pragma unroll
+        for (int p = p0; p < SR; ++p) u = u + cmulc(a[p][q], vr[p]);   // conj(a_ij) v_i
+        v[q] = u.x;
+        v[V / 2 + q] = u.y;
+        r += u.x * vc[q].x + u.y * vc[q].y;
+      }
+      msum_level<V, 0, V>(v, lane);
+      r = wave_sum(r);
+      if (msum_writer<V>(tr)) {
+        const int sl = msum_slot<V>(tr), q = sl % (V / 2);
+        if (q < SC) reinterpret_cast<double*>(&s_y[tc + TC * q])[sl / (V / 2)] = v[0];
+      }
+      if (lane == 0) s_r[tid >> 6] = r;
+      __syncthreads();
+      // 2. w, column c, its reflector
+      double R = 0.0;
+#pragma unroll
+      for (int k = 0; k < NW; ++k) R += s_r[k];
+      const double al = -0.5 * (t.x * t.x + t.y * t.y) * R;
+      c128 wr[SR];
+#pragma unroll
+      for (int p = p0; p < SR; ++p) {
+        const c128 u = cmul(t, s_y[tr + 16 * p]);
+        wr[p] = c128{u.x + al * vr[p].x, u.y + al * vr[p].y};
+      }
+      auto update = [&](int q) {
+        const c128 u = cmul(t, s_y[tc + TC * q]);
+        const c128 cw = c128{u.x + al * vc[q].x, -(u.y + al * vc[q].y)}, cv = cconj(vc[q]);
+#pragma unroll
+        for (int p = p0; p < SR; ++p) {
+          const c128 u1 = cmul(vr[p], cw), u2 = cmul(wr[p], cv);
+          a[p][q] = c128{a[p][q].x - u1.x - u2.x, a[p][q].y - u1.y - u2.y};
+        }
+      };
+      update(qc);
+      double dg = 0.0, xx = 0.0, ax = 0.0, ay = 0.0;
+#pragma unroll
+      for (int p = p0; p < SR; ++p) {
+        const int i = tr + 16 * p;
+        const c128 x = a[p][qc];
+        if (i == c) dg = x.x;
+        if (i == c + 1) { ax = x.x; ay = x.y; }
+        if (i >= c + 2) xx += x.x * x.x + x.y * x.y;   // rows past the block are zero
+      }
+      dg = row_sum(dg);
+      xx = row_sum(xx);
+      const Refl h = householder_fast(c128{row_sum(ax), row_sum(ay)}, xx);
+      if (tc == cc) {
+#pragma unroll
+        for (int p = p0; p < SR; ++p) {
+          const int i = tr + 16 * p;
+          const c128 vi = i == c + 1 ? c128{1.0, 0.0} : (i > c + 1 ? cmul(a[p][qc], h.scale) : c128{0.0, 0.0});
+          s_v[i] = vi;
+          if (i > c && i < m) A[(size_t)(base + c) * ld + base + i] = vi;
+        }
+        if (tr == 0) {
+          d[base + c] = dg;
+          s_t = h.tau;
+          if (c + 1 < m) {
+            e[base + c] = h.beta;
+            tau[base + c] = h.tau;
+          }
+        }
+      }
+#pragma unroll
+      for (int q = qc + 1; q < SC; ++q) update(q);
+      __syncthreads();
+      // 3. the new reflector
+      t = s_t;
+#pragma unroll
+      for (int p = p0; p < SR; ++p) vr[p] = s_v[tr + 16 * p];
+#pragma unroll
+      for (int q = qc; q < SC; ++q) vc[q] = tc + TC * q > c ? s_v[tc + TC * q] : c128{0.0, 0.0};
+    }
+  }
+}
+
+// the block [base, n) of at most kRegTridiagN rows
+void tridiag_reg(int n, int base, bool pending, c128* A, int ld, double* d, double* e, c128* tau, const int* info,
+                 hipStream_t st) {
+  const int m = n - base, pd = pending ? 1 : 0;
+  if (m <= 32) k_tridiag_reg<16, 2, 2><<<1, 256, 0, st>>>(n, base, pd, A, ld, d, e, tau, info);
+  else if (m <= 48) k_tridiag_reg<16, 3, 3><<<1, 256, 0, st>>>(n, base, pd, A, ld, d, e, tau, info);
+  else if (m <= 64) k_tridiag_reg<16, 4, 4><<<1, 256, 0, st>>>(n, base, pd, A, ld, d, e, tau, info);
+  else k_tridiag_reg<32, 6, 3><<<1, 512, 0, st>>>(n, base, pd, A, ld, d, e, tau, info);
 }
 
 // ---------------------------------------------------------------------------
@@ -1816,7 +2026,8 @@ pw_status pw::heig_solve(HeigWork& hw, int n0, int n, int nev, const c128* H, co
   PW_TRY(pw::zgemm_nn_sk(n, n, n, 1.0, H, ld, hw.X, ldw, 0.0, hw.T1, ldw, part, skb, st));
   PW_TRY((pw::zgemm_cn<double, double, double>(n, n, n, hw.X, ldw, hw.T1, ldw, hw.A, ldw, part,
                                                part_bytes, st)));
-  const bool coop_tri = hw.coop_ok && n >= kCoopMinN && n <= kCoopMaxN;
+  const bool reg_tri = hw.block_tri && n <= kRegTridiagN;
+  const bool coop_tri = hw.coop_ok && !reg_tri && n >= kCoopMinN && n <= kCoopMaxN;
   k_isolate<<<std::min(1024, ceil_div(n * n, 256)), 256, 0, st>>>(
       n, hw.A, ldw, hw.drop, hw.info, coop_tri ? coop_buf(hw).count : nullptr, coop_tri ? coop_buf(hw).fail : nullptr,
       coop_tri ? coop_buf(hw).go : nullptr, hw.gamma);
@@ -1825,6 +2036,10 @@ pw_status pw::heig_solve(HeigWork& hw, int n0, int n, int nev, const c128* H, co
     pw::ProfScope ps(pw::PK_TRIDIAG, st, 16.0 / 3.0 * n * n * (double)n);
     if (coop_tri) {
       const CoopBuf cb = coop_buf(hw);   // counter and flag cleared by k_isolate
+      // the last kRegTridiagN rows in one workgroup: a column takes 2.0 us
+      // there, 3.7 with a barrier across the device.  The handover leaves
+      // reflector kstop - 1 pending, so kstop >= 2
+      const int kstop = hw.block_tri ? std::max(2, n - kRegTridiagN) : n + 1;   // n + 1: never
       const bool wide = hw.coop_wide;
       // beyond 512 rows a solve that runs alone keeps 8 rows per workgroup,
       // in passes of 512 columns (up to one workgroup per CU at 2048 rows):
@@ -1836,16 +2051,19 @@ pw_status pw::heig_solve(HeigWork& hw, int n0, int n, int nev, const c128* H, co
       // up to 512 rows: 8 rows per workgroup (twice the workgroups, half the
       // update work per step on each) unless the wide form is asked for; beyond, 16
       if (big8 && n <= 4 * CB)
-        k_tridiag_coop<2, 8, 2 * CB><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb);
+        k_tridiag_coop<2, 8, 2 * CB><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
       else if (big8)
-        k_tridiag_coop<4, 8, 2 * CB><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb);
-      else if (n <= CB && !wide) k_tridiag_coop<1, 8><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb);
-      else if (n <= CB) k_tridiag_coop<1, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb);
+        k_tridiag_coop<4, 8, 2 * CB><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+      else if (n <= CB && !wide) k_tridiag_coop<1, 8><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+      else if (n <= CB) k_tridiag_coop<1, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
       else if (n <= 2 * CB && !wide)
-        k_tridiag_coop<2, 8><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb);
-      else if (n <= 2 * CB) k_tridiag_coop<2, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb);
-      else if (n <= 4 * CB) k_tridiag_coop<4, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb);
-      else k_tridiag_coop<8, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb);
+        k_tridiag_coop<2, 8><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+      else if (n <= 2 * CB) k_tridiag_coop<2, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+      else if (n <= 4 * CB) k_tridiag_coop<4, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+      else k_tridiag_coop<8, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+      if (hw.block_tri) tridiag_reg(n, kstop, true, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, st);
+    } else if (reg_tri) {
+      tridiag_reg(n, 0, false, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, st);
     } else if (n <= kPanelMinN) {
       k_tridiag<<<1, NTL, sizeof(c128) * (2 * n + std::max(n, NTL)), st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau,
                                                                           hw.info);
