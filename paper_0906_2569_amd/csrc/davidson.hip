@@ -743,15 +743,21 @@ extern "C" pw_status davidson_solve(pw_plan p, int32_t nb, pw_c128* psi_u, int32
     }
     if (f.info != 0) {
       // the newest corrections made the overlap singular: the Ritz vectors
-      // were not replaced; collapse onto them once and try again
+      // were not replaced; start afresh from them (H psi and the reduced
+      // matrices formed anew: what accumulated in the carried ones is part of
+      // the trouble) and go on
       if (retried || nbase == nb - S.nl) { result = pw::fail(PW_EBREAKDOWN, "reduced overlap matrix not positive definite"); break; }
       retried = true;
-      PW_HIP(hipMemsetAsync(W.hw.info, 0, sizeof(int), st));
-      PW_TRY(S.collapse(nb - S.nl));
+      PW_HIP(hipMemcpy2DAsync(W.phi, sizeof(c128) * W.ld, W.psi + (size_t)S.nl * W.ld, sizeof(c128) * W.ld,
+                              sizeof(c128) * npw, nb - S.nl, hipMemcpyDeviceToDevice, st));
+      PW_TRY(S.start_block(prec, nb - S.nl));
       nbase = nb - S.nl;
+      amp = 1.0;
       stats.restarts++;
+      stats.fresh_starts++;
       continue;
     }
+    retried = false;   // this factorization held: a later singular one is collapsed again, not the end
     if (f.nan) { result = pw::fail(PW_ENAN, "non-finite residual norm"); break; }
     if (p->cancel.exchange(0)) { result = pw::fail(PW_ECANCELLED, "solve cancelled (pw_cancel)"); break; }
     if (fp32_stage && f.maxr < kStallZone * o.ladder_switch) {

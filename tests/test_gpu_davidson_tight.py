@@ -1,0 +1,28 @@
+"""Davidson solves to residuals of 1e-10 Ha whose corrections make the reduced
+overlap singular more than once on the way: the solve starts afresh from its
+Ritz vectors each time instead of ending in PW_EBREAKDOWN."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_0906_2569_amd import pwgen
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.mark.parametrize("seed", [11, 26, 55])
+def test_repeated_singular_overlap(seed):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_0906_2569_amd import pwdft
+    p = pwgen.make_cell(10.0, 15.0, 8, 16, seed, nr=(30, 30, 30))
+    w = oracle.eigh_lowest(oracle.dense_h_of(p), p.nb)[0]
+    ctx = pwdft.Context(0)
+    plan = pwdft.Plan(ctx, p, nb_max=p.nb, ndim_max=4)
+    x = torch.from_numpy(p.psi0).cuda()
+    st, eig, resid, _ = plan.davidson(x, opts=pwdft.default_opts(ndim=4, tol_resid=1e-10))
+    assert st in (0, 1)
+    np.testing.assert_allclose(eig.cpu().numpy(), w, atol=5e-9, rtol=0)
+    ctx.close()
