@@ -5,11 +5,14 @@
 //   ||drho||^2 = 4 pi omega sum_{G != 0} |drho(G)|^2 / |G|^2,  drho(G) = (1/N) sum_j drho(r_j) exp(-i G.r_j)
 //
 // The density reuses the first half of the H.psi transforms: the inverse z
-// pass onto the sticks and the inverse y pass of every plane into the plane
-// copies ([band][z][y][x column]).  One workgroup then owns a strip of rows
-// of one plane and runs the inverse x transforms of those rows for every band
-// of the chunk in order, accumulating w_b |psi_b|^2 in LDS: the band sum is
-// done in a fixed order, with no atomics, so the result is reproducible.
+// pass onto the sticks, then the inverse y and x transforms of each plane.
+// Where the two-step plane kernels cover the grid, one workgroup per (plane,
+// group of transforms) runs both in LDS and registers and keeps the plane's
+// band sum in registers (k_density_wave), and k_density_sum adds the groups.
+// Other grids write the y transforms to the plane copies ([band][z][y][x
+// column]), and one workgroup per strip of rows runs the x transforms of every
+// band in order, accumulating w_b |psi_b|^2 in LDS.  Either way the band sum
+// has a fixed order and no atomics: the result is reproducible.
 //
 // The norm transforms drho on the full grid (three passes of batched 1D
 // transforms along x, y and z through HBM) and sums the weighted squares in a
@@ -17,6 +20,7 @@
 #include <cmath>
 
 #include "plan.h"
+#include "plane_wave.h"
 #include "profile.h"
 
 namespace {
@@ -66,6 +70,18 @@ k_density_x(SphereMap m, const c128* __restrict__ rows, int nt, int nbands, int 
   for (int e = threadIdx.x; e < nr * n1; e += blockDim.x) {
     const double v = acc[e] * inv_omega;
     out[e] = add ? out[e] + v : v;
+  }
+}
+
+// rho (+)= inv_omega sum_g part[g], in increasing g
+__global__ void __launch_bounds__(DTHREADS)
+k_density_sum(size_t n, int groups, const double* __restrict__ part, double inv_omega, int add,
+              double* __restrict__ rho) {
+  for (size_t i = blockIdx.x * (size_t)blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+    double s = 0.0;
+    for (int g = 0; g < groups; ++g) s += part[(size_t)g * n + i];
+    s *= inv_omega;
+    rho[i] = add ? rho[i] + s : s;
   }
 }
 
@@ -203,14 +219,40 @@ extern "C" pw_status pw_density(pw_plan p, int32_t nb, const pw_c128* psi, int32
   // transforms: one per band, or one per pair of bands at Gamma
   const bool gam = p->gamma;
   const int nt = gam ? ceil_div(nb, 2) : nb;
+  // grids of the two-step plane kernels, where the workspace holds a grid of
+  // partial sums: the plane stays in LDS and registers (72^3, 128 bands: 1018
+  // -> 200 us, 160 of them the plane kernel, bound by its float64 vector work).  Other grids go through the plane copies.
+  const pw::PlaneWave<double> wv = pw::plane_wave_f64(p->n1, p->n2);
+  const size_t wlds = wv.density ? wv.lds(p->nxr, 1, wv.density_waves) : 0;
+  const bool wave = wv.density != nullptr &&
+                    (size_t)p->band_chunk * p->n3 * p->n2 * p->nxr * sizeof(c128) >= sizeof(double) * (size_t)p->N;
+  if (wave) PW_TRY(pw::raise_lds_limit((const void*)wv.density, (int)wlds));
   for (int c0 = 0; c0 < nt; c0 += p->band_chunk) {
     const int ntc = std::min(p->band_chunk, nt - c0);
     const int b0 = gam ? 2 * c0 : c0;
     const int nbb = gam ? std::min(nb - b0, 2 * ntc) : ntc;
+    const int add = (accumulate || c0 > 0) ? 1 : 0;
+    if (wave) {
+      // transforms in groups: about four workgroups per CU over planes x
+      // groups, as many partial grids as the plane-copy workspace holds (the
+      // first workgroups of a group wait on their sticks: more of them hide it)
+      const size_t room = (size_t)p->band_chunk * p->n3 * p->n2 * p->nxr * sizeof(c128) / (sizeof(double) * p->N);
+      const int groups = std::max(1, std::min({ntc, ceil_div(1024, p->n3), (int)std::min<size_t>(room, 1024)}));
+      const int per = ceil_div(ntc, groups), ng = ceil_div(ntc, per);
+      PW_TRY(pw::psi_to_sticks(p, ntc, nbb, psi_c + (size_t)b0 * ldpsi, ldpsi, s));
+      double* part = static_cast<double*>(p->rows);
+      wv.density<<<dim3(p->n3, ng), 64 * wv.density_waves, wlds, s>>>(m, static_cast<const c128*>(p->sticks), ntc, per,
+                                                                     nbb, gam ? 1 : 0, w + b0, p->tw64_1, p->tw64_2,
+                                                                     part);
+      k_density_sum<<<std::min(2048, ceil_div(p->N, DTHREADS)), DTHREADS, 0, s>>>((size_t)p->N, ng, part, 1.0 / omega,
+                                                                                 add, rho);
+      PW_HIP(hipGetLastError());
+      continue;
+    }
     PW_TRY(pw::psi_to_rows(p, ntc, nbb, psi_c + (size_t)b0 * ldpsi, ldpsi, s));
     k_density_x<<<dim3(p->n3, ceil_div(p->n2, DCB)), DTHREADS, lds, s>>>(
         m, static_cast<const c128*>(p->rows), ntc, nbb, gam ? 1 : 0, w + b0, p->tw64_1, 1.0 / omega,
-        (accumulate || c0 > 0) ? 1 : 0, rho);
+        add, rho);
     PW_HIP(hipGetLastError());
   }
   return PW_OK;

@@ -29,11 +29,24 @@
 #include "profile.h"
 #include "zpass.h"
 
+// raise a kernel's dynamic LDS limit (above the default 64 KB) once per kernel
+pw_status pw::raise_lds_limit(const void* fn, int bytes) {
+  static std::mutex mu;
+  static std::map<const void*, int> raised;
+  std::lock_guard<std::mutex> lk(mu);
+  auto it = raised.find(fn);
+  if (it != raised.end() && it->second >= bytes) return PW_OK;
+  PW_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
+  raised[fn] = bytes;
+  return PW_OK;
+}
+
 namespace {
 
 using pw::ZFns;
 using pw::gamma_pack;
 using pw::to_t;
+using pw::raise_lds_limit;
 using pw::z_tile;
 
 constexpr int ZSB = 16;        // sticks per workgroup in the z passes
@@ -504,18 +517,6 @@ PlaneRegFn<T> plane_reg_kernel(int n1, int n2) {
 constexpr size_t kPlaneRegMaxLds = 80 * 1024;
 // largest LDS of the one-plane register kernel (static LDS of the kernel is nil)
 constexpr size_t kPlaneRegMaxLds1 = 156 * 1024;
-
-// raise a kernel's dynamic LDS limit (above the default 64 KB) once per kernel
-pw_status raise_lds_limit(const void* fn, int bytes) {
-  static std::mutex mu;
-  static std::map<const void*, int> raised;
-  std::lock_guard<std::mutex> lk(mu);
-  auto it = raised.find(fn);
-  if (it != raised.end() && it->second >= bytes) return PW_OK;
-  PW_HIP(hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, bytes));
-  raised[fn] = bytes;
-  return PW_OK;
-}
 
 template <typename T>
 size_t plane_reg_lds_bytes(int n, int nxr, int pp) {
@@ -1955,14 +1956,12 @@ pw_status hpsi_fft(pw_plan p, int nb, const c128* psi, int ldpsi, c128* hpsi, in
 }
 }  // namespace
 
-pw_status pw::psi_to_rows(pw_plan p, int nt, int nbands, const c128* psi, int ldpsi, hipStream_t s) {
-  PW_CHECK(p->rows != nullptr, PW_EINVAL, "plan has no plane-copy workspace (create it with opts.density = 1)");
+pw_status pw::psi_to_sticks(pw_plan p, int nt, int nbands, const c128* psi, int ldpsi, hipStream_t s) {
   PW_CHECK(nt >= 0 && nt <= p->band_chunk, PW_EINVAL, "more transforms than one chunk");
   PW_CHECK(p->gamma ? (nbands <= 2 * nt && nbands >= 2 * nt - 1) || (nt == 0 && nbands == 0) : nbands == nt,
            PW_EINVAL, "band count does not match the transform count");
   if (nt == 0) return PW_OK;
   const SphereMap m = p->map();
-  const cpx<double>* tw2 = (const cpx<double>*)p->tw64_2;
   const cpx<double>* tw3 = (const cpx<double>*)p->tw64_3;
   cpx<double>* st = static_cast<cpx<double>*>(p->sticks);
   const ZFns<double> zr = z_fns<double>(p->n3);
@@ -1979,6 +1978,17 @@ pw_status pw::psi_to_rows(pw_plan p, int nt, int nbands, const c128* psi, int ld
   } else {
     k_zinv<double><<<gz * nt8, ZTHREADS, zl, s>>>(m, psi, ldpsi, st, tw3, gz, nt);
   }
+  PW_HIP(hipGetLastError());
+  return PW_OK;
+}
+
+pw_status pw::psi_to_rows(pw_plan p, int nt, int nbands, const c128* psi, int ldpsi, hipStream_t s) {
+  PW_CHECK(p->rows != nullptr, PW_EINVAL, "plan has no plane-copy workspace (create it with opts.density = 1)");
+  PW_TRY(pw::psi_to_sticks(p, nt, nbands, psi, ldpsi, s));
+  if (nt == 0) return PW_OK;
+  const SphereMap m = p->map();
+  const cpx<double>* tw2 = (const cpx<double>*)p->tw64_2;
+  const cpx<double>* st = static_cast<const cpx<double>*>(p->sticks);
   k_plane_yinv<double><<<dim3(p->n3, nt, ceil_div(p->nxr, SPLIT_CB)), SPLIT_THREADS,
                          split_lds_bytes<double>(p->n1, p->n2), s>>>(m, st, static_cast<cpx<double>*>(p->rows), tw2);
   PW_HIP(hipGetLastError());

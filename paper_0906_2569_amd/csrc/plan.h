@@ -165,6 +165,10 @@ void plan_destroy(pw_plan p);
 // transform per band (nt = nbands), or at Gamma one per pair of bands
 // (nt = ceil(nbands / 2), psi_2t + i psi_2t+1)
 pw_status psi_to_rows(pw_plan p, int nt, int nbands, const c128* psi, int ldpsi, hipStream_t stream);
+// its first half: sphere -> sticks
+pw_status psi_to_sticks(pw_plan p, int nt, int nbands, const c128* psi, int ldpsi, hipStream_t stream);
+// raise a kernel's dynamic LDS limit above the default 64 KB (once per kernel and size)
+pw_status raise_lds_limit(const void* fn, int bytes);
 // H.psi for nb bands (nb <= opts.nb_max) on `stream`.
 pw_status hpsi_launch(pw_plan p, pw_precision prec, int nb, const c128* psi, int ldpsi,
                       c128* hpsi, int ldhpsi, hipStream_t stream);

@@ -8,6 +8,10 @@ namespace pw {
 template <typename T>
 struct PlaneWave {
   void (*fn)(SphereMap, cpx<T>*, const T*, const cpx<T>*, const cpx<T>*, int) = nullptr;
+  // density of transforms [0, nt): groups of `per` transforms along grid.y (k_density_wave)
+  void (*density)(SphereMap, const c128*, int, int, int, int, const double*, const c128*, const c128*,
+                  double*) = nullptr;
+  int density_waves = 0;
   int ys = 0;           // LDS stride of an x column
   int wave_words = 0;   // exchange words (of T) of a wave
   int rows = 0, cols = 0;   // rows / x columns a wave transforms at a time

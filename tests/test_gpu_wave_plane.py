@@ -85,3 +85,46 @@ def test_gamma_pairs(ctx, n):
     ref = oracle.hpsi(oracle.dense_h_of(g.full), g.expand(g.psi0))
     err = (np.linalg.norm(got - ref, axis=1) / np.linalg.norm(ref, axis=1)).max()
     assert err <= 1e-11, err
+
+
+# band sums over groups of transforms: one band, fewer than and more than one per group
+@pytest.mark.parametrize("nb", [1, 5, 40])
+@pytest.mark.parametrize("nr", [(24, 24, 30), (30, 30, 25), (50, 45, 27), (60, 60, 24), (72, 72, 24), (96, 100, 25),
+                                (120, 120, 25), (128, 128, 24)])
+def test_density(ctx, nr, nb):
+    from paper_0906_2569_amd import pwdft
+    p = _box_cell(70 + nr[0] + nb, nr, nb, ng=60)
+    w = np.random.default_rng(nb).uniform(0.0, 2.0, nb)
+    plan = pwdft.Plan(ctx, p, precision=0, nb_max=nb, ndim_max=0, density=1)
+    x = torch.from_numpy(p.psi0).cuda()
+    got = plan.density(x, w, 275.0)
+    again = plan.density(x, w, 275.0).cpu().numpy()
+    twice = plan.density(x, w, 275.0, rho=got.clone(), accumulate=True).cpu().numpy()
+    got = got.cpu().numpy()
+    plan.close()
+    f = np.zeros((nb, nr[2], nr[1], nr[0]), dtype=complex)
+    m = p.miller
+    f[:, m[:, 2] % nr[2], m[:, 1] % nr[1], m[:, 0] % nr[0]] = p.psi0
+    r = np.fft.ifftn(f, axes=(1, 2, 3)) * (nr[0] * nr[1] * nr[2])
+    ref = np.einsum("b,bzyx->zyx", w, r.real ** 2 + r.imag ** 2) / 275.0
+    # rounding of three transforms (about 2 log2 N ulp of the largest value) and of the band sum
+    tol = 1e-13 * np.abs(ref).max()
+    np.testing.assert_allclose(got, ref, atol=tol, rtol=0)
+    np.testing.assert_array_equal(got, again)
+    np.testing.assert_allclose(twice, 2 * ref, atol=2 * tol, rtol=0)
+
+
+@pytest.mark.parametrize("n", [45, 72])
+def test_density_gamma(ctx, n):
+    from paper_0906_2569_amd import pwdft
+    g = pwgen.gamma_cell(6.5, 20.0, 2, 5, 960 + n, nr=(n, n, n))
+    w = np.array([2.0, 1.0, 0.5, 0.0, 1.5])
+    plan = pwdft.Plan(ctx, g, precision=0, nb_max=5, ndim_max=0, density=1, gamma=1)
+    got = plan.density(torch.from_numpy(g.psi0).cuda(), w, 100.0).cpu().numpy()
+    plan.close()
+    f = np.zeros((5, n, n, n), dtype=complex)
+    m = g.full.miller
+    f[:, m[:, 2] % n, m[:, 1] % n, m[:, 0] % n] = g.expand(g.psi0)
+    r = np.fft.ifftn(f, axes=(1, 2, 3)) * n ** 3
+    ref = np.einsum("b,bzyx->zyx", w, r.real ** 2 + r.imag ** 2) / 100.0
+    np.testing.assert_allclose(got, ref, atol=1e-13 * np.abs(ref).max(), rtol=0)
