@@ -50,9 +50,18 @@ __device__ __forceinline__ int rrow<double>(int lane, int q) { return 4 * q + (l
 
 constexpr int BM = 64, BN = 64, BK = 32, NT = 256;
 
+// One K slice in LDS, row k holding its M (N) entries.  Reads take 16
+// neighbouring entries of four rows: rows k and k + 1 lie half the banks
+// apart (float64; a quarter in float32).  Writes take one entry of 32 rows
+// (tn, and B of nn): within a row entry c sits at c ^ s(k), s spreading the
+// rows that share a bank offset over 16 entries.
 template <typename T>
 struct RTile {
-  T a[BK][BM + 1], b[BK][BN + 1];
+  static constexpr int pad = 16;
+  T a[BK][BM + pad], b[BK][BN + pad];
+  static __device__ __forceinline__ int at(int k, int c) {
+    return c ^ (sizeof(T) == 8 ? (k >> 1) & 15 : ((k >> 2) & 7) << 1);
+  }
 };
 
 // workgroups of one output tile range share an XCD (round-robin launch order)
@@ -78,12 +87,12 @@ __device__ __forceinline__ void rtile_mma(const RTile<T>& t, typename RMma<T>::v
   const int r = lane & 15, kq = lane >> 4;
 #pragma unroll
   for (int k4 = 0; k4 < BK; k4 += 4) {
-    const int kk = k4 + kq;
+    const int kk = k4 + kq, rs = RTile<T>::at(kk, r);   // at() stays within aligned groups of 16
     T a[2], b[2];
 #pragma unroll
     for (int i = 0; i < 2; ++i) {
-      a[i] = t.a[kk][wm * 32 + i * 16 + r];
-      b[i] = t.b[kk][wn * 32 + i * 16 + r];
+      a[i] = t.a[kk][wm * 32 + i * 16 + rs];
+      b[i] = t.b[kk][wn * 32 + i * 16 + rs];
     }
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -110,30 +119,52 @@ k_dgemm_tn(int M, int N, int K, int kchunk, const TA* __restrict__ A, long lda, 
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) c[i][j] = v4{0, 0, 0, 0};
-  constexpr int PER = BM * BK / NT;
+  // the next K slice is loaded while the current one is multiplied; rows past
+  // M and columns past N read the last one (not stored), so full slices need no
+  // checks (offsets: a plan's grid bounds npw, 63 lda stays within 32 bits)
+  constexpr int PER = BM * BK / NT, RP = NT / BK;
+  const int kk = threadIdx.x % BK, r0 = threadIdx.x / BK;
+  const TA* a0 = A + (size_t)m0 * lda + kbeg;
+  const TB* b0 = B + (size_t)n0 * ldb + kbeg;
+  unsigned oa[PER], ob[PER];
+#pragma unroll
+  for (int it = 0; it < PER; ++it) {
+    oa[it] = (unsigned)min(r0 + it * RP, M - 1 - m0) * (unsigned)lda + kk;
+    ob[it] = (unsigned)min(r0 + it * RP, N - 1 - n0) * (unsigned)ldb + kk;
+  }
+  const int klen = max(kend - kbeg, 0), nfull = klen / BK, rem = klen % BK, nslice = nfull + (rem ? 1 : 0);
   TA ra[PER];
   TB rb[PER];
-  auto load = [&](int k0) {
+  auto load = [&](int sl) {
+    if (sl < nfull) {
 #pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int kk = idx % BK, mi = idx / BK;
-      const int k = k0 + kk;
-      ra[it] = (m0 + mi < M && k < kend) ? A[(size_t)(m0 + mi) * lda + k] : TA(0);
-      rb[it] = (n0 + mi < N && k < kend) ? B[(size_t)(n0 + mi) * ldb + k] : TB(0);
+      for (int it = 0; it < PER; ++it) {
+        ra[it] = a0[oa[it]];
+        rb[it] = b0[ob[it]];
+      }
+      a0 += BK;
+      b0 += BK;
+    } else {   // the last, partial slice: zeros past its end
+      const bool in = kk < rem;
+      const int back = in ? 0 : kk - (rem - 1);
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        const TA va = a0[oa[it] - back];
+        const TB vb = b0[ob[it] - back];
+        ra[it] = in ? va : TA(0);
+        rb[it] = in ? vb : TB(0);
+      }
     }
   };
-  if (kbeg < kend) load(kbeg);
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
+  if (nslice > 0) load(0);
+  for (int sl = 0; sl < nslice; ++sl) {
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int kk = idx % BK, mi = idx / BK;
-      t.a[kk][mi] = (T)ra[it];
-      t.b[kk][mi] = (T)rb[it];
+      t.a[kk][RTile<T>::at(kk, r0 + it * RP)] = (T)ra[it];
+      t.b[kk][RTile<T>::at(kk, r0 + it * RP)] = (T)rb[it];
     }
     __syncthreads();
-    if (k0 + BK < kend) load(k0 + BK);
+    if (sl + 1 < nslice) load(sl + 1);
     rtile_mma<T>(t, c, wm, wn, lane);
     __syncthreads();
   }
@@ -196,33 +227,47 @@ k_dgemm_nn(int M, int N, int K, double alpha, const TA* __restrict__ A, long lda
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) c[i][j] = v4{0, 0, 0, 0};
-  constexpr int PER = BM * BK / NT;
+  constexpr int PER = BM * BK / NT, AP = NT / BM, RP = NT / BK;
+  const int mi = threadIdx.x % BM, ka = threadIdx.x / BM;   // A: this thread's row, first k
+  const int kk = threadIdx.x % BK, r0 = threadIdx.x / BK;   // B: its k, first column
+  const TA* pa = A + (size_t)ka * lda + min(m0 + mi, M - 1);
+  const TB* pb[PER];
+#pragma unroll
+  for (int it = 0; it < PER; ++it) pb[it] = B + (size_t)min(n0 + r0 + it * RP, N - 1) * ldb + kk;
+  const size_t astep = (size_t)AP * lda, aslice = (size_t)BK * lda;
+  const int nfull = max(K, 0) / BK, rem = max(K, 0) % BK, nslice = nfull + (rem ? 1 : 0);
   TA ra[PER];
   TB rb[PER];
-  auto load = [&](int k0) {
+  auto load = [&](int sl) {
+    if (sl < nfull) {
 #pragma unroll
-    for (int it = 0; it < PER; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      {
-        const int mi = idx % BM, kk = idx / BM;
-        ra[it] = (m0 + mi < M && k0 + kk < K) ? A[(size_t)(k0 + kk) * lda + m0 + mi] : TA(0);
+      for (int it = 0; it < PER; ++it) {
+        ra[it] = pa[it * astep];
+        rb[it] = *pb[it];
+        pb[it] += BK;
       }
-      {
-        const int kk = idx % BK, ni = idx / BK;
-        rb[it] = (n0 + ni < N && k0 + kk < K) ? B[(size_t)(n0 + ni) * ldb + k0 + kk] : TB(0);
+      pa += aslice;
+    } else {   // the last, partial slice: zeros past its end
+#pragma unroll
+      for (int it = 0; it < PER; ++it) {
+        const int k = ka + it * AP;
+        const TA va = *(pa + ((long)min(k, rem - 1) - ka) * lda);
+        const TB vb = pb[it][min(kk, rem - 1) - kk];
+        ra[it] = k < rem ? va : TA(0);
+        rb[it] = kk < rem ? vb : TB(0);
       }
     }
   };
-  if (K > 0) load(0);
-  for (int k0 = 0; k0 < K; k0 += BK) {
+  if (nslice > 0) load(0);
+  for (int sl = 0; sl < nslice; ++sl) {
 #pragma unroll
     for (int it = 0; it < PER; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      t.a[idx / BM][idx % BM] = (T)ra[it];
-      t.b[idx % BK][idx / BK] = (T)rb[it];
+      const int k = ka + it * AP;
+      t.a[k][RTile<T>::at(k, mi)] = (T)ra[it];
+      t.b[kk][RTile<T>::at(kk, r0 + it * RP)] = (T)rb[it];
     }
     __syncthreads();
-    if (k0 + BK < K) load(k0 + BK);
+    if (sl + 1 < nslice) load(sl + 1);
     rtile_mma<T>(t, c, wm, wn, lane);
     __syncthreads();
   }

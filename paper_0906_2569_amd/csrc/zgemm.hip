@@ -58,26 +58,29 @@ template <>
 __device__ __forceinline__ int mrow<double>(int lane, int q) { return 4 * q + (lane >> 4); }
 __device__ __forceinline__ int mcol(int lane) { return lane & 15; }
 
-// The float32 GEMM kernels are built for at least three waves per SIMD (at
-// most 168 registers, spill-free): three 64x64 tiles then share a CU, and a
-// product of 18277 x 128 rows and columns (572 tiles) is resident in one
-// round.  The float64 ones hold three float64 accumulator sets (96
-// registers) and are built for two waves per SIMD, each MFMA there taking
-// twice as many cycles.
+// Both kernels are bound by the matrix cores; what they lose is the time in
+// which no wave of a SIMD has products ready (a K slice takes a fetch, an LDS
+// store and two barriers).  So the loads of a full slice carry no bounds
+// checks (a check per load split the fetch into branches: 512-atom cell in
+// float32 22.5 -> 20.5 ms calbec, 21.0 -> 19.2 ms add-back), calbec keeps two
+// slices in flight, and the add-back runs at three waves per SIMD (168
+// registers; float64, 200 atoms: 2649 us at two waves, 2477 at three).
+// Accumulators must stay in VGPRs: with AGPR accumulators the float64 MFMA
+// issues at 48 instead of 77 TFLOP/s.
 constexpr int BN = 64, BK = 16, NT = 256;
 // Output tile rows per workgroup (BM) and waves per SIMD the kernels are
 // built for.  The calbec-shaped product (k_gemm_cn) in float32 takes 128 rows
-// (each wave a 64 x 32 block of 4 x 2 MFMA tiles: twice the products per
-// operand byte loaded and per LDS read of a 64 x 64 tile; 22.4 against
-// 23.7 ms at the 512-atom cell) at two waves per SIMD; the add-back
-// (k_gemm_nn) keeps 64 rows, which measured faster there (20.9 against
-// 21.4 ms), at three; float64 takes 64 rows at two waves per SIMD (its three
-// accumulator sets).
+// at two waves per SIMD (each wave a 64 x 32 block of 4 x 2 MFMA tiles: twice
+// the products per operand byte loaded and per LDS read of a 64 x 64 tile;
+// 22.4 against 23.7 ms at the 512-atom cell) unless 64 balance the CUs better
+// (launch_cn), at three; the add-back (k_gemm_nn) 64 rows; float64 calbec 64
+// rows at two waves (three accumulator sets and two slices in flight).  BM of
+// k_gemm_cn also fixes the K split, and with it the rounding.
 template <typename T, bool CN>
 struct GT {
   static constexpr int BM = (sizeof(T) == 4 && CN) ? 128 : 64;
   static constexpr int IM = BM / 32;   // 16-row MFMA tiles per wave (two waves along M)
-  static constexpr int waves = (sizeof(T) == 4 && !CN) ? 3 : 2;
+  static constexpr int waves = 3;      // of k_gemm_nn
 };
 
 // Workgroups go to the 8 XCDs round-robin in linear launch order.  Each XCD is
@@ -102,9 +105,26 @@ __device__ __forceinline__ void xcd_block(int& bx, int& by, int& bz) {
   bz = w / (gx * gy);
 }
 
-template <typename T, int BM>
+// One K slice of the operands in LDS, row k holding the slice's M (N) entries;
+// real and imaginary parts apart, or (IL) together as 16-byte entries (float64
+// k_gemm_nn: 2442 against 2477 us for the 200-atom add-back; in float32, and in
+// k_gemm_cn with its transposing writes, slower: 24.4 against 20.5 ms for the
+// 512-atom calbec, 3267 against 2839 us for the float64 200-atom one).
+template <typename T, int BM, bool IL>
 struct Tile {
   T ar[BK][BM + 1], ai[BK][BM + 1], br[BK][BN + 1], bi[BK][BN + 1];
+  __device__ __forceinline__ void put_a(int k, int m, cpx<T> v) { ar[k][m] = v.x; ai[k][m] = v.y; }
+  __device__ __forceinline__ void put_b(int k, int n, cpx<T> v) { br[k][n] = v.x; bi[k][n] = v.y; }
+  __device__ __forceinline__ cpx<T> get_a(int k, int m) const { return cpx<T>{ar[k][m], ai[k][m]}; }
+  __device__ __forceinline__ cpx<T> get_b(int k, int n) const { return cpx<T>{br[k][n], bi[k][n]}; }
+};
+template <typename T, int BM>
+struct Tile<T, BM, true> {
+  cpx<T> a[BK][BM + 1], b[BK][BN + 1];
+  __device__ __forceinline__ void put_a(int k, int m, cpx<T> v) { a[k][m] = v; }
+  __device__ __forceinline__ void put_b(int k, int n, cpx<T> v) { b[k][n] = v; }
+  __device__ __forceinline__ cpx<T> get_a(int k, int m) const { return a[k][m]; }
+  __device__ __forceinline__ cpx<T> get_b(int k, int n) const { return b[k][n]; }
 };
 
 // Accumulators of one wave's 32x32 quadrant (2x2 blocks of 16x16): a = t1,
@@ -135,8 +155,8 @@ struct CAcc {
 
 // One BK slice of a BM x 64 tile product held in LDS; each of the 4 waves
 // owns a (BM / 2) x 32 block (IM x 2 MFMA tiles of 16 x 16).
-template <typename T, int BM>
-__device__ __forceinline__ void tile_mma(const Tile<T, BM>& t, CAcc<T, BM / 32>& acc, int wm, int wn, int lane) {
+template <typename T, int BM, bool IL>
+__device__ __forceinline__ void tile_mma(const Tile<T, BM, IL>& t, CAcc<T, BM / 32>& acc, int wm, int wn, int lane) {
   constexpr int IM = BM / 32, WM = BM / 2;
   const int r = lane & 15, kq = lane >> 4;
 #pragma unroll
@@ -145,13 +165,15 @@ __device__ __forceinline__ void tile_mma(const Tile<T, BM>& t, CAcc<T, BM / 32>&
     T ar[IM], ai[IM], br[2], bi[2];
 #pragma unroll
     for (int i = 0; i < IM; ++i) {
-      ar[i] = t.ar[kk][wm * WM + i * 16 + r];
-      ai[i] = t.ai[kk][wm * WM + i * 16 + r];
+      const cpx<T> v = t.get_a(kk, wm * WM + i * 16 + r);
+      ar[i] = v.x;
+      ai[i] = v.y;
     }
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      br[j] = t.br[kk][wn * 32 + j * 16 + r];
-      bi[j] = t.bi[kk][wn * 32 + j * 16 + r];
+      const cpx<T> v = t.get_b(kk, wn * 32 + j * 16 + r);
+      br[j] = v.x;
+      bi[j] = v.y;
     }
     if constexpr (CAcc<T, IM>::k3) {
       T sa[IM], sb[2];
@@ -184,12 +206,12 @@ __device__ __forceinline__ void tile_mma(const Tile<T, BM>& t, CAcc<T, BM / 32>&
 // partial[z][n][m] = sum_{k in chunk z} conj(A[m*lda + k]) B[n*ldb + k]
 // gridDim.z = 2 nsplit for two products of one launch: z >= nsplit takes B1
 // and writes the partials after those of the first product
-template <typename T, typename TA, typename TB>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(GT<T, true>::waves)))
+template <typename T, typename TA, typename TB, int BM>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && BM == 64 ? 3 : 2)))
 k_gemm_cn(int M, int N, int K, int kchunk, int nsplit, const cpx<TA>* __restrict__ A, int lda,
           const cpx<TB>* __restrict__ B0, const cpx<TB>* __restrict__ B1, int ldb, cpx<T>* __restrict__ P) {
-  constexpr int BM = GT<T, true>::BM, IM = GT<T, true>::IM;
-  __shared__ Tile<T, BM> t;
+  constexpr int IM = BM / 32;
+  __shared__ Tile<T, BM, false> t;
   int bx, by, bz;
   xcd_block<false>(bx, by, bz);   // the output tiles of one K chunk share an XCD
   const int m0 = bx * BM, n0 = by * BN;
@@ -201,47 +223,64 @@ k_gemm_cn(int M, int N, int K, int kchunk, int nsplit, const cpx<TA>* __restrict
   CAcc<T, IM> acc;
   acc.zero();
 
-  // the next K slice is loaded into registers while the current one is
-  // multiplied out of LDS
+  // Two K slices are in flight in registers while one is multiplied out of
+  // LDS: under this kernel's load a fetch takes longer than one slice's
+  // products.  Rows past M and columns past N read the last one (their
+  // products are not stored), so the loads of a full slice need no checks.
   constexpr int PA = BM * BK / NT, PB = BN * BK / NT;
-  cpx<TA> ra[PA];
-  cpx<TB> rb[PB];
-  auto load = [&](int k0) {
+  const int kk = threadIdx.x % BK;
+  const int r0 = threadIdx.x / BK;
+  const cpx<TA>* pa[PA];
+  const cpx<TB>* pb[PB];
 #pragma unroll
-    for (int it = 0; it < PA; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int kk = idx % BK, mi = idx / BK;
-      const int k = k0 + kk, m = m0 + mi;
-      ra[it] = (m < M && k < kend) ? A[(size_t)m * lda + k] : cpx<TA>{TA(0), TA(0)};
-    }
+  for (int it = 0; it < PA; ++it) pa[it] = A + (size_t)min(m0 + r0 + it * (NT / BK), M - 1) * lda + kbeg + kk;
 #pragma unroll
-    for (int it = 0; it < PB; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int kk = idx % BK, ni = idx / BK;
-      const int k = k0 + kk, n = n0 + ni;
-      rb[it] = (n < N && k < kend) ? B[(size_t)n * ldb + k] : cpx<TB>{TB(0), TB(0)};
+  for (int it = 0; it < PB; ++it) pb[it] = B + (size_t)min(n0 + r0 + it * (NT / BK), N - 1) * ldb + kbeg + kk;
+  const int klen = max(kend - kbeg, 0), nfull = klen / BK, rem = klen % BK, nslice = nfull + (rem ? 1 : 0);
+  cpx<TA> ra[2][PA];
+  cpx<TB> rb[2][PB];
+  auto load = [&](cpx<TA>(&xa)[PA], cpx<TB>(&xb)[PB], int sl) {
+    if (sl < nfull) {
+#pragma unroll
+      for (int it = 0; it < PA; ++it) { xa[it] = *pa[it]; pa[it] += BK; }
+#pragma unroll
+      for (int it = 0; it < PB; ++it) { xb[it] = *pb[it]; pb[it] += BK; }
+    } else {   // the last, partial slice: zeros past its end
+      const bool in = kk < rem;
+      const int back = in ? 0 : rem - 1 - kk;
+#pragma unroll
+      for (int it = 0; it < PA; ++it) {
+        const cpx<TA> v = pa[it][back];
+        xa[it] = in ? v : cpx<TA>{TA(0), TA(0)};
+      }
+#pragma unroll
+      for (int it = 0; it < PB; ++it) {
+        const cpx<TB> v = pb[it][back];
+        xb[it] = in ? v : cpx<TB>{TB(0), TB(0)};
+      }
     }
   };
-  if (kbeg < kend) load(kbeg);
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
+  auto slice = [&](cpx<TA>(&xa)[PA], cpx<TB>(&xb)[PB], int sl) {
 #pragma unroll
     for (int it = 0; it < PA; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int kk = idx % BK, mi = idx / BK;
-      t.ar[kk][mi] = (T)ra[it].x;
-      t.ai[kk][mi] = -(T)ra[it].y;  // conj(A)
+      const int mi = r0 + it * (NT / BK);
+      t.put_a(kk, mi, cpx<T>{(T)xa[it].x, -(T)xa[it].y});  // conj(A)
     }
 #pragma unroll
     for (int it = 0; it < PB; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int kk = idx % BK, ni = idx / BK;
-      t.br[kk][ni] = (T)rb[it].x;
-      t.bi[kk][ni] = (T)rb[it].y;
+      const int ni = r0 + it * (NT / BK);
+      t.put_b(kk, ni, cpx<T>{(T)xb[it].x, (T)xb[it].y});
     }
     __syncthreads();
-    if (k0 + BK < kend) load(k0 + BK);
-    tile_mma<T, BM>(t, acc, wm, wn, lane);
+    if (sl + 2 < nslice) load(xa, xb, sl + 2);
+    tile_mma(t, acc, wm, wn, lane);
     __syncthreads();
+  };
+  if (nslice > 0) load(ra[0], rb[0], 0);
+  if (nslice > 1) load(ra[1], rb[1], 1);
+  for (int sl = 0; sl < nslice; sl += 2) {
+    slice(ra[0], rb[0], sl);
+    if (sl + 1 < nslice) slice(ra[1], rb[1], sl + 1);
   }
   cpx<T>* out = P + (size_t)bz * M * N;
 #pragma unroll
@@ -276,51 +315,61 @@ k_gemm_nn(int M, int N, int K, double alpha, const cpx<TA>* __restrict__ A0, con
   const int kbeg = SPLIT ? bz * kchunk : 0;
   const int kend = SPLIT ? min(K, kbeg + kchunk) : K;
   constexpr int BM = GT<T, false>::BM, IM = GT<T, false>::IM;
-  __shared__ Tile<T, BM> t;
+  __shared__ Tile<T, BM, sizeof(T) == 8> t;
   const int m0 = bx * BM, n0 = by * BN;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wm = wave & 1, wn = wave >> 1;
   CAcc<T, IM> acc;
   acc.zero();
 
+  // the next K slice is loaded while the current one is multiplied; rows past
+  // M and columns past N read the last one (not stored)
   constexpr int PA = BM * BK / NT, PB = BN * BK / NT;
+  const int mi = threadIdx.x % BM, ka = threadIdx.x / BM;   // A: this thread's row, first k
+  const int kk = threadIdx.x % BK, nb = threadIdx.x / BK;   // B: its k, first column
+  const cpx<TA>* pa = A + (size_t)(kbeg + ka) * lda + min(m0 + mi, M - 1);
+  const cpx<TB>* pb[PB];
+#pragma unroll
+  for (int it = 0; it < PB; ++it) pb[it] = B + (size_t)min(n0 + nb + it * (NT / BK), N - 1) * ldb + kbeg + kk;
+  const size_t astep = (size_t)(NT / BM) * lda, aslice = (size_t)BK * lda;
+  const int klen = max(kend - kbeg, 0), nfull = klen / BK, rem = klen % BK, nslice = nfull + (rem ? 1 : 0);
   cpx<TA> ra[PA];
   cpx<TB> rb[PB];
-  auto load = [&](int k0) {
+  auto load = [&](int sl) {
+    if (sl < nfull) {
 #pragma unroll
-    for (int it = 0; it < PA; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int mi = idx % BM, kk = idx / BM;
-      const int m = m0 + mi, k = k0 + kk;
-      ra[it] = (m < M && k < kend) ? A[(size_t)k * lda + m] : cpx<TA>{TA(0), TA(0)};
-    }
+      for (int it = 0; it < PA; ++it) ra[it] = pa[it * astep];
+      pa += aslice;
 #pragma unroll
-    for (int it = 0; it < PB; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int kk = idx % BK, ni = idx / BK;
-      const int n = n0 + ni, k = k0 + kk;
-      rb[it] = (n < N && k < kend) ? B[(size_t)n * ldb + k] : cpx<TB>{TB(0), TB(0)};
+      for (int it = 0; it < PB; ++it) { rb[it] = *pb[it]; pb[it] += BK; }
+    } else {   // the last, partial slice: zeros past its end
+#pragma unroll
+      for (int it = 0; it < PA; ++it) {
+        const int k = ka + it * (NT / BM);
+        const cpx<TA> v = *(pa + ((long)min(k, rem - 1) - ka) * lda);
+        ra[it] = k < rem ? v : cpx<TA>{TA(0), TA(0)};
+      }
+#pragma unroll
+      for (int it = 0; it < PB; ++it) {
+        const cpx<TB> v = pb[it][min(kk, rem - 1) - kk];
+        rb[it] = kk < rem ? v : cpx<TB>{TB(0), TB(0)};
+      }
     }
   };
-  if (kbeg < kend) load(kbeg);
-  for (int k0 = kbeg; k0 < kend; k0 += BK) {
+  if (nslice > 0) load(0);
+  for (int sl = 0; sl < nslice; ++sl) {
 #pragma unroll
     for (int it = 0; it < PA; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int mi = idx % BM, kk = idx / BM;
-      t.ar[kk][mi] = (T)ra[it].x;
-      t.ai[kk][mi] = (T)ra[it].y;
+      const int k = ka + it * (NT / BM);
+      t.put_a(k, mi, cpx<T>{(T)ra[it].x, (T)ra[it].y});
     }
 #pragma unroll
     for (int it = 0; it < PB; ++it) {
-      const int idx = threadIdx.x + it * NT;
-      const int kk = idx % BK, ni = idx / BK;
-      t.br[kk][ni] = (T)rb[it].x;
-      t.bi[kk][ni] = (T)rb[it].y;
+      t.put_b(kk, nb + it * (NT / BK), cpx<T>{(T)rb[it].x, (T)rb[it].y});
     }
     __syncthreads();
-    if (k0 + BK < kend) load(k0 + BK);
-    tile_mma<T, BM>(t, acc, wm, wn, lane);
+    if (sl + 1 < nslice) load(sl + 1);
+    tile_mma(t, acc, wm, wn, lane);
     __syncthreads();
   }
   if constexpr (SPLIT) {
@@ -466,6 +515,28 @@ struct Split {
   int nsplit, kchunk;
 };
 
+// Launch of k_gemm_cn with ns K chunks in all (two products: twice the
+// splits).  The chunks, hence the rounding, are the caller's; the tile height
+// is free.  float32 takes 128 rows unless 64 fill the 256 CUs so much better
+// that they win in spite of their lower intensity (6% at the 512-atom cell):
+// the fullest CU's rows decide.  (200-atom calbec, 539 workgroups of 128 rows
+// or 1001 of 64: 2.26 against 1.62 ms.)
+template <typename T, typename TA, typename TB>
+void launch_cn(int M, int N, int K, int kchunk, int nsplit, int ns, const cpx<TA>* A, int lda, const cpx<TB>* B0,
+               const cpx<TB>* B1, int ldb, cpx<T>* P, hipStream_t s) {
+  constexpr int cus = 256;
+  const int gy = ceil_div(N, BN);
+  if constexpr (GT<T, true>::BM == 128) {
+    const long wide = ceil_div((long)ceil_div(M, 128) * gy * ns, cus), half = ceil_div((long)ceil_div(M, 64) * gy * ns, cus);
+    if (100 * 128 * wide <= 106 * 64 * half) {
+      k_gemm_cn<T, TA, TB, 128><<<dim3(ceil_div(M, 128), gy, ns), NT, 0, s>>>(M, N, K, kchunk, nsplit, A, lda, B0, B1,
+                                                                            ldb, P);
+      return;
+    }
+  }
+  k_gemm_cn<T, TA, TB, 64><<<dim3(ceil_div(M, 64), gy, ns), NT, 0, s>>>(M, N, K, kchunk, nsplit, A, lda, B0, B1, ldb, P);
+}
+
 Split choose_split(int M, int N, int K, int BM) {
   const int tiles = ceil_div(M, BM) * ceil_div(N, BN);
   const int target = 512;
@@ -515,8 +586,7 @@ pw_status pw::zgemm_cn(int M, int N, int K, const cpx<TA>* A, int lda, const cpx
   }
   {
     pw::ProfScope ps(pw::PK_GEMM_CN, s, 8.0 * M * N * K);
-    k_gemm_cn<T, TA, TB><<<dim3(ceil_div(M, GT<T, true>::BM), ceil_div(N, BN), sp.nsplit), NT, 0, s>>>(
-        M, N, K, sp.kchunk, sp.nsplit, A, lda, B, B, ldb, P);
+    launch_cn<T>(M, N, K, sp.kchunk, sp.nsplit, sp.nsplit, A, lda, B, B, ldb, P, s);
   }
   {
     pw::ProfScope ps(pw::PK_GEMM_RED, s, (double)sp.nsplit * M * N * sizeof(cpx<T>) + 16.0 * M * N);
@@ -543,8 +613,7 @@ pw_status pw::zgemm_cn_pair(int M, int N, int K, const c128* A, int lda, const c
   c128* P = static_cast<c128*>(part);
   {
     pw::ProfScope ps(pw::PK_GEMM_CN, s, 16.0 * M * N * K);
-    k_gemm_cn<double, double, double><<<dim3(ceil_div(M, GT<double, true>::BM), ceil_div(N, BN), 2 * nsplit), NT, 0, s>>>(
-        M, N, K, kchunk, nsplit, A, lda, B0, B1, ldb, P);
+    launch_cn<double>(M, N, K, kchunk, nsplit, 2 * nsplit, A, lda, B0, B1, ldb, P, s);
   }
   {
     pw::ProfScope ps(pw::PK_GEMM_RED, s, 2.0 * ((double)nsplit * M * N * sizeof(c128) + 16.0 * M * N));
@@ -567,8 +636,7 @@ pw_status pw::calbec_d(pw_plan p, int nb, const c128* psi, int ldpsi, cpx<T>* ou
   const cpx<T>* drow = rows ? rows : (sizeof(T) == 8 ? (const cpx<T>*)p->drow64 : (const cpx<T>*)p->drow32);
   {
     pw::ProfScope ps(pw::PK_CALBEC, s, 8.0 * M * N * K);
-    k_gemm_cn<T, T, double><<<dim3(ceil_div(M, GT<T, true>::BM), ceil_div(N, BN), sp.nsplit), NT, 0, s>>>(
-        M, N, K, sp.kchunk, sp.nsplit, beta, p->ldb, psi, psi, ldpsi, P);
+    launch_cn<T>(M, N, K, sp.kchunk, sp.nsplit, sp.nsplit, beta, p->ldb, psi, psi, ldpsi, P, s);
   }
   {
     pw::ProfScope ps(pw::PK_CALBEC_RED, s, (double)sp.nsplit * M * N * sizeof(cpx<T>) + (double)M * N * sizeof(cpx<T>));
