@@ -389,6 +389,7 @@ pw_status pw::dav_alloc(pw_plan p) {
   PW_TRY(get(pw::heig_work_bytes((int)nbx), &hwb));
   PW_TRY(pw::heig_setup(W->hw, hwb, (int)nbx));
   W->hw.block_tri = true;
+  W->hw.herm_mean = true;
   void* hf = nullptr;
   PW_TRY(pw::host_alloc(p, sizeof(DavFlags), &hf));
   W->hflags = static_cast<DavFlags*>(hf);

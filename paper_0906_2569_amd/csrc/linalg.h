@@ -28,6 +28,8 @@ struct HeigWork {
                            // registers (the Davidson solver).  Off for the bare reduced solver:
                            // an eigenvector's sign there follows the rounding of the inverse
                            // iteration's shift, so its callers keep the reduction they had
+  bool herm_mean = false;  // reduce the Hermitian part of the transformed matrix (the Davidson solver,
+                           // where its triangles can differ by 1e-11); off for the bare solver as above
   int cus = 0;             // compute units of the device (set by heig_setup)
   double drop_tol = 1e-10; // Cholesky pivot, relative to the original diagonal entry, below which
                            // a basis direction counts as dependent (lies, to the accuracy of S,

@@ -432,10 +432,18 @@ __global__ void k_zero_block(int r0, int r1, int c1, c128* __restrict__ X, int l
 // launch also clears gamma and, when the cooperative tridiagonalization
 // follows, its barrier counter, failure flag and release flags (coop_count,
 // coop_fail, coop_go; null otherwise).
+//
+// mean: A becomes its Hermitian part.  A = X^H (H X) is formed entry by entry,
+// and where the basis is nearly dependent (overlap condition 1e6, |X| 200) its
+// triangles differ by 1e-11 among the newest directions.  The reduction takes
+// A v for (v^H A)^H; the difference lands on the wanted rows, where it set a
+// floor of 1e-9 to 1e-7 under the residuals of a solve (8 atoms, 16 bands, tol
+// 1e-10: 37 of 100 starts ran to the limit of 200 iterations; with the mean
+// none does).
 __global__ void k_isolate(int n, c128* __restrict__ A, int ld, const int* __restrict__ drop,
                           const int* __restrict__ info, unsigned* __restrict__ coop_count,
                           unsigned* __restrict__ coop_fail, unsigned* __restrict__ coop_go,
-                          double* __restrict__ gamma) {
+                          double* __restrict__ gamma, bool mean) {
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     *gamma = 0.0;   // maximum taken by k_colnorms at the end of the solve
     if (coop_count != nullptr) {
@@ -447,7 +455,17 @@ __global__ void k_isolate(int n, c128* __restrict__ A, int ld, const int* __rest
   if (*info != 0) return;
   for (int idx = blockIdx.x * blockDim.x + threadIdx.x; idx < n * n; idx += gridDim.x * blockDim.x) {
     const int i = idx % n, j = idx / n;
-    if (drop[i] || drop[j]) A[(size_t)j * ld + i] = c128{(i == j) ? 1e12 : 0.0, 0.0};
+    if (mean) {
+      if (i > j) continue;   // the pair is its upper entry's
+      const bool out = drop[i] || drop[j];
+      c128 *up = A + (size_t)j * ld + i, *lo = A + (size_t)i * ld + j;
+      const c128 u = *up, l = *lo;
+      const c128 m = out ? c128{(i == j) ? 1e12 : 0.0, 0.0} : c128{0.5 * (u.x + l.x), 0.5 * (u.y - l.y)};
+      *up = m;
+      *lo = c128{m.x, -m.y};
+    } else if (drop[i] || drop[j]) {
+      A[(size_t)j * ld + i] = c128{(i == j) ? 1e12 : 0.0, 0.0};
+    }
   }
 }
 
@@ -2030,7 +2048,7 @@ pw_status pw::heig_solve(HeigWork& hw, int n0, int n, int nev, const c128* H, co
   const bool coop_tri = hw.coop_ok && !reg_tri && n >= kCoopMinN && n <= kCoopMaxN;
   k_isolate<<<std::min(1024, ceil_div(n * n, 256)), 256, 0, st>>>(
       n, hw.A, ldw, hw.drop, hw.info, coop_tri ? coop_buf(hw).count : nullptr, coop_tri ? coop_buf(hw).fail : nullptr,
-      coop_tri ? coop_buf(hw).go : nullptr, hw.gamma);
+      coop_tri ? coop_buf(hw).go : nullptr, hw.gamma, hw.herm_mean);
   // tridiagonalize, eigenvalues, eigenvectors of T, back-transform
   {
     pw::ProfScope ps(pw::PK_TRIDIAG, st, 16.0 / 3.0 * n * n * (double)n);

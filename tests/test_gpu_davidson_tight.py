@@ -26,3 +26,22 @@ def test_repeated_singular_overlap(seed):
     assert st in (0, 1)
     np.testing.assert_allclose(eig.cpu().numpy(), w, atol=5e-9, rtol=0)
     ctx.close()
+
+
+@pytest.mark.parametrize("seed,lock", [(2, 1), (3, 0), (11, 0), (12, 1), (14, 1)])
+def test_residual_reaches_the_tolerance(seed, lock):
+    # nearly dependent bases on the way: the rounding of the reduced problem
+    # must not put a floor under the residuals (one of 1e-9 did: 200 iterations
+    # used up).  100 iterations are 1.5 times what these cells need
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_0906_2569_amd import pwdft
+    p = pwgen.make_cell(10.0, 15.0, 8, 16, seed, nr=(30, 30, 30))
+    ctx = pwdft.Context(0)
+    plan = pwdft.Plan(ctx, p, nb_max=p.nb, ndim_max=4)
+    x = torch.from_numpy(p.psi0).cuda()
+    st, _, resid, stats = plan.davidson(
+        x, opts=pwdft.default_opts(ndim=4, tol_resid=1e-10, max_iter=100, lock=lock))
+    assert st == 0
+    assert float(resid.max()) <= 2e-10
+    ctx.close()
