@@ -2049,10 +2049,15 @@ pw_status nonlocal_side(pw_plan p, int nb, const c128* psi, int ldpsi, c128* hps
 // Does the projector term run on the side stream, beside the transforms?  By
 // default yes, unless the plane pass of this precision holds a whole CU's LDS
 // with one workgroup (no room for the GEMM waves beside it: they only slow
-// each other down) or takes the three-kernel form.
-bool nl_beside(pw_plan p, bool f64) {
+// each other down), takes the three-kernel form, or the product is small.
+bool nl_beside(pw_plan p, bool f64, int nb) {
   if (p->opts.nl_overlap == 1) return true;
   if (p->opts.nl_overlap == 2) return false;
+  // Small float64 products: the fork and join of a second stream cost more
+  // than the kernels gain side by side (8 atoms, one band: 60 us beside, 35
+  // after; 28 atoms, 14 bands: 91 and 80; but 56 bands 127 and 139, and 64
+  // atoms, 8 bands 153 and 160)
+  if (f64 && (double)p->nbeta * p->npw <= 2e6 && (double)nb * p->npw <= 2e5) return false;
   const int form = f64 ? p->form64 : p->form32;
   switch (form) {
     case kFormSplit: return false;
@@ -2064,7 +2069,10 @@ bool nl_beside(pw_plan p, bool f64) {
     case kFormQuad:
       return (f64 ? plane_reg_lds_bytes<double>(p->n1, p->nxr, 1) : plane_reg_lds_bytes<float>(p->n1, p->nxr, 1)) <=
              kPlaneRegMaxLds;
-    default: return true;
+    default:
+      // a two-step plane workgroup of 120^2 and more takes a CU's LDS and
+      // registers (256-atom Gamma block: 7.28 ms after, 7.84 beside)
+      return !(f64 && p->n2 >= 120 && plane_wave_of<double>(p->n1, p->n2, p->nxr).fn != nullptr);
   }
 }
 
@@ -2080,7 +2088,7 @@ pw_status pw::hpsi_launch(pw_plan p, pw_precision prec, int nb, const c128* psi,
     return f64 ? nonlocal_side<double>(p, nb, psi, ldpsi, hpsi, ldhpsi, ns)
                : nonlocal_side<float>(p, nb, psi, ldpsi, hpsi, ldhpsi, ns);
   };
-  if (p->nbeta > 0 && !nl_beside(p, f64)) {
+  if (p->nbeta > 0 && !nl_beside(p, f64, nb)) {
     // projector term first, on the caller's stream; the transforms add to it
     PW_TRY(nonlocal(s));
   } else if (p->nbeta > 0) {
