@@ -773,7 +773,9 @@ __global__ void k_tridiag_last(int n, const c128* __restrict__ A, int ld, double
 // registers.  Rows are dealt cyclically (row r to workgroup r mod P), so every
 // workgroup keeps about (n - k) / P live rows at step k; thread t holds
 // columns t mod CBW + CBW c (c < NC) of a 512 / CBW-th of its workgroup's
-// rows (two waves per SIMD; CBW = 256 or 512 columns per pass).
+// rows (CBW = 256 or 512 columns per pass).  Up to 512 rows a workgroup is 256
+// threads: a step's chain (the sums, w, the reflector) is the same in every
+// wave and bound by issue, so one wave per SIMD runs it faster than two.
 //
 // Step k (the reflector v_k, tau_k is known in every workgroup, and every
 // workgroup holds y = B v_k for its rows):
@@ -833,12 +835,6 @@ __device__ __forceinline__ double dpp_f64(double v) {
   const int hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
-__device__ __forceinline__ double readlane_f64(double v, int l) {
-  const long long b = __double_as_longlong(v);
-  const int lo = __builtin_amdgcn_readlane((int)(b & 0xffffffffll), l);
-  const int hi = __builtin_amdgcn_readlane((int)(b >> 32), l);
-  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
-}
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppMirror = 0x140;
 template <int LEVEL>
 __device__ __forceinline__ double row_partner(double v) {
@@ -848,6 +844,30 @@ __device__ __forceinline__ double row_partner(double v) {
   else return dpp_f64<kDppMirror>(v);
 }
 
+// v plus the value of lane i ^ 16, and of lane i ^ 32: a swap of 16- or 32-lane
+// rows between two copies of v leaves the two terms side by side (registers
+// only; through ds_bpermute each took a trip to LDS)
+template <bool HALF>
+__device__ __forceinline__ double swap_sum(double v) {
+  const long long b = __double_as_longlong(v);
+  const unsigned lo = (unsigned)b, hi = (unsigned)((unsigned long long)b >> 32);
+  double x, y;
+  if constexpr (HALF) {
+    const auto l = __builtin_amdgcn_permlane32_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(hi, hi, false, false);
+    x = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0]));
+    y = __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(lo, lo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(hi, hi, false, false);
+    x = __longlong_as_double((long long)(((unsigned long long)h[0] << 32) | l[0]));
+    y = __longlong_as_double((long long)(((unsigned long long)h[1] << 32) | l[1]));
+  }
+  return x + y;
+}
+__device__ __forceinline__ double row_pair_sum(double v) { return swap_sum<false>(v); }
+__device__ __forceinline__ double half_sum(double v) { return swap_sum<true>(v); }
+
 // sum of one double over the 64 lanes; every lane ends with the same bits
 // (each pairwise sum is formed from the same two operands, and the four row
 // sums are combined in one fixed order)
@@ -856,7 +876,7 @@ __device__ __forceinline__ double wave_sum(double v) {
   v += row_partner<1>(v);
   v += row_partner<2>(v);
   v += row_partner<3>(v);
-  return (readlane_f64(v, 0) + readlane_f64(v, 16)) + (readlane_f64(v, 32) + readlane_f64(v, 48));
+  return half_sum(row_pair_sum(v));
 }
 
 // sum over the 64 lanes of the V values in v[] (V a power of two <= 16).  The
@@ -891,8 +911,7 @@ template <int V>
 __device__ __forceinline__ void wave_multi_sum(double (&v)[V]) {
   static_assert(V >= 1 && V <= 16 && (V & (V - 1)) == 0, "V a power of two <= 16");
   msum_level<V, 0, V>(v, threadIdx.x & 63);
-  v[0] += __shfl_xor(v[0], 16, 64);
-  v[0] += __shfl_xor(v[0], 32, 64);
+  v[0] = half_sum(row_pair_sum(v[0]));
 }
 template <int V>
 constexpr int ilog2c() { return V <= 1 ? 0 : 1 + ilog2c<V / 2>(); }
@@ -926,12 +945,47 @@ __device__ __forceinline__ Refl householder(c128 al, double xn2) {
   return r;
 }
 
-template <int NC, int CRT, int CBW = CB>
-__global__ void __launch_bounds__(CT) k_tridiag_coop(int n, c128* __restrict__ A, int ld, double* __restrict__ d,
+// 1 / sqrt(s) and 1 / x to float64 rounding from the hardware estimates (two
+// Newton steps): a much shorter dependent chain than the IEEE sequences
+__device__ __forceinline__ double newton_rsqrt(double s) {
+  double r = __builtin_amdgcn_rsq(s);
+  r = fma(0.5 * r, fma(-s * r, r, 1.0), r);
+  return fma(0.5 * r, fma(-s * r, r, 1.0), r);
+}
+__device__ __forceinline__ double newton_rcp(double x) {
+  double r = __builtin_amdgcn_rcp(x);
+  r = fma(r, fma(-x, r, 1.0), r);
+  return fma(r, fma(-x, r, 1.0), r);
+}
+
+// householder() with the square root and the divisions through the above;
+// sums of squares out of their range take householder() itself
+__device__ __forceinline__ Refl householder_fast(c128 al, double xn2) {
+  const double s = al.x * al.x + al.y * al.y + xn2;
+  if (!(s > 1e-280 && s < 1e280)) return householder(al, xn2);
+  Refl r;
+  if (xn2 == 0.0 && al.y == 0.0) {
+    r.tau = c128{0.0, 0.0}; r.beta = al.x; r.scale = c128{0.0, 0.0};
+    return r;
+  }
+  const double q = newton_rsqrt(s), nrm0 = s * q;
+  const double nrm = fma(0.5 * q, fma(-nrm0, nrm0, s), nrm0);   // sqrt(s) to the last place
+  const double sg = al.x >= 0.0 ? -1.0 : 1.0;
+  const double beta = sg * nrm, ib = sg * q;
+  r.beta = beta;
+  r.tau = c128{(beta - al.x) * ib, -al.y * ib};
+  const c128 den = c128{al.x - beta, al.y};
+  const double id = newton_rcp(den.x * den.x + den.y * den.y);
+  r.scale = c128{den.x * id, -den.y * id};
+  return r;
+}
+
+template <int NC, int CRT, int CBW = CB, int NT = CT, bool FAST = false>
+__global__ void __launch_bounds__(NT) k_tridiag_coop(int n, c128* __restrict__ A, int ld, double* __restrict__ d,
                                                      double* __restrict__ e, c128* __restrict__ tau,
                                                      int* __restrict__ info, CoopBuf cb, int kstop) {
-  constexpr int NW = CT / 64;             // waves
-  constexpr int NH = CT / CBW;            // row groups (threads t and t + CBW share columns)
+  constexpr int NW = NT / 64;             // waves
+  constexpr int NH = NT / CBW;            // row groups (threads t and t + CBW share columns)
   constexpr int RH = CRT / NH;            // rows per thread
   constexpr int WH = CBW / 64;            // waves per row group
   if (*info != 0) return;
@@ -942,6 +996,10 @@ __global__ void __launch_bounds__(CT) k_tridiag_coop(int n, c128* __restrict__ A
   __shared__ c128 s_alx;
   __shared__ int s_fail;
 
+  auto reflector = [](c128 al, double xn2) {
+    if constexpr (FAST) return householder_fast(al, xn2);
+    else return householder(al, xn2);
+  };
   const int P = gridDim.x, q = blockIdx.x, tid = threadIdx.x;
   const int lane = tid & 63, wid = tid >> 6;
   const int half = tid / CBW;
@@ -950,10 +1008,15 @@ __global__ void __launch_bounds__(CT) k_tridiag_coop(int n, c128* __restrict__ A
   auto row_of = [&](int i) { return q + P * i; };
   // local index of row r if it is an own row, else -1
   auto local_of = [&](int r) { return (r >= q && (r - q) % P == 0 && (r - q) / P < CRT) ? (r - q) / P : -1; };
-  int jc[NC];
+  int jc[NC], own[NC];
   bool ok[NC];
 #pragma unroll
-  for (int c = 0; c < NC; ++c) { jc[c] = (tid % CBW) + CBW * c; ok[c] = jc[c] < n; }
+  for (int c = 0; c < NC; ++c) {
+    jc[c] = (tid % CBW) + CBW * c;
+    ok[c] = jc[c] < n;
+    // (one copy of the columns, the first row group's, writes the own rows)
+    own[c] = half == 0 && ok[c] ? local_of(jc[c]) : -1;
+  }
 
   // rows of B: a[c][i] = B[row(half RH + i)][j_c] = conj(A[row * ld + j_c])
   c128 a[NC][RH];
@@ -970,14 +1033,11 @@ __global__ void __launch_bounds__(CT) k_tridiag_coop(int n, c128* __restrict__ A
   if (tid < CRT) { s_rv[0][tid] = s_rv[1][tid] = s_rw[tid] = c128{0.0, 0.0}; }
   __syncthreads();
 
-  // own-row values of a column vector to LDS (one copy: the first half writes)
+  // own-row values of a column vector to LDS
   auto put_own = [&](c128* dst, const c128 (&val)[NC]) {
-    if (half != 0) return;
 #pragma unroll
-    for (int c = 0; c < NC; ++c) {
-      const int li = local_of(jc[c]);
-      if (li >= 0 && ok[c]) dst[li] = val[c];
-    }
+    for (int c = 0; c < NC; ++c)
+      if (own[c] >= 0) dst[own[c]] = val[c];
   };
   // y = B v on the own rows: per-thread partial sums, then per-wave totals to s_red
   auto rows_times = [&](const c128 (&acc)[RH]) {
@@ -1008,7 +1068,7 @@ __global__ void __launch_bounds__(CT) k_tridiag_coop(int n, c128* __restrict__ A
     const double r = wave_sum(xx);
     if (lane == 0) s_xn2[wid] = r;
     __syncthreads();
-    const Refl h = householder(s_alx, wave_sum(lane < NW ? s_xn2[lane] : 0.0));
+    const Refl h = reflector(s_alx, wave_sum(lane < NW ? s_xn2[lane] : 0.0));
 #pragma unroll
     for (int c = 0; c < NC; ++c)
       vk[c] = (jc[c] == 1) ? c128{1.0, 0.0} : (jc[c] > 1 && ok[c] ? cmul(x[c], h.scale) : c128{0.0, 0.0});
@@ -1147,7 +1207,7 @@ __global__ void __launch_bounds__(CT) k_tridiag_coop(int n, c128* __restrict__ A
     }
     __syncthreads();
     // 4. every wave: reflector k+1 (identical everywhere)
-    const Refl h = householder(s_alx, wave_sum(lane < NW ? s_xn2[lane] : 0.0));
+    const Refl h = reflector(s_alx, wave_sum(lane < NW ? s_xn2[lane] : 0.0));
     c128 vk1[NC];
 #pragma unroll
     for (int c = 0; c < NC; ++c) {
@@ -1238,41 +1298,6 @@ __device__ __forceinline__ double row_sum(double v) {
   v += row_partner<2>(v);
   v += row_partner<3>(v);
   return v;
-}
-
-// 1 / sqrt(s) and 1 / x to float64 rounding from the hardware estimates (two
-// Newton steps): a much shorter dependent chain than the IEEE sequences
-__device__ __forceinline__ double newton_rsqrt(double s) {
-  double r = __builtin_amdgcn_rsq(s);
-  r = fma(0.5 * r, fma(-s * r, r, 1.0), r);
-  return fma(0.5 * r, fma(-s * r, r, 1.0), r);
-}
-__device__ __forceinline__ double newton_rcp(double x) {
-  double r = __builtin_amdgcn_rcp(x);
-  r = fma(r, fma(-x, r, 1.0), r);
-  return fma(r, fma(-x, r, 1.0), r);
-}
-
-// householder() with the square root and the divisions through the above;
-// sums of squares out of their range take householder() itself
-__device__ __forceinline__ Refl householder_fast(c128 al, double xn2) {
-  const double s = al.x * al.x + al.y * al.y + xn2;
-  if (!(s > 1e-280 && s < 1e280)) return householder(al, xn2);
-  Refl r;
-  if (xn2 == 0.0 && al.y == 0.0) {
-    r.tau = c128{0.0, 0.0}; r.beta = al.x; r.scale = c128{0.0, 0.0};
-    return r;
-  }
-  const double q = newton_rsqrt(s), nrm0 = s * q;
-  const double nrm = fma(0.5 * q, fma(-nrm0, nrm0, s), nrm0);   // sqrt(s) to the last place
-  const double sg = al.x >= 0.0 ? -1.0 : 1.0;
-  const double beta = sg * nrm, ib = sg * q;
-  r.beta = beta;
-  r.tau = c128{(beta - al.x) * ib, -al.y * ib};
-  const c128 den = c128{al.x - beta, al.y};
-  const double id = newton_rcp(den.x * den.x + den.y * den.y);
-  r.scale = c128{den.x * id, -den.y * id};
-  return r;
 }
 
 template <int TC, int SR, int SC>
@@ -2068,17 +2093,20 @@ pw_status pw::heig_solve(HeigWork& hw, int n0, int n, int nev, const c128* H, co
       const int P = big8 ? ceil_div(n, 8) : pw::coop_workgroups(n, wide);
       // up to 512 rows: 8 rows per workgroup (twice the workgroups, half the
       // update work per step on each) unless the wide form is asked for; beyond, 16
-      if (big8 && n <= 4 * CB)
-        k_tridiag_coop<2, 8, 2 * CB><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
-      else if (big8)
-        k_tridiag_coop<4, 8, 2 * CB><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
-      else if (n <= CB && !wide) k_tridiag_coop<1, 8><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
-      else if (n <= CB) k_tridiag_coop<1, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+      // (block_tri: the reflectors may round differently, see there)
+      const bool fast = hw.block_tri;
+      auto go = [&](auto kernel, int threads) {
+        kernel<<<P, threads, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+      };
+      if (big8 && n <= 4 * CB) go(k_tridiag_coop<2, 8, 2 * CB>, CT);
+      else if (big8) go(k_tridiag_coop<4, 8, 2 * CB>, CT);
+      else if (n <= CB && !wide) fast ? go(k_tridiag_coop<1, 8, CB, CB, true>, CB) : go(k_tridiag_coop<1, 8, CB, CB>, CB);
+      else if (n <= CB) go(k_tridiag_coop<1, CR, CB, CB>, CB);
       else if (n <= 2 * CB && !wide)
-        k_tridiag_coop<2, 8><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
-      else if (n <= 2 * CB) k_tridiag_coop<2, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
-      else if (n <= 4 * CB) k_tridiag_coop<4, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
-      else k_tridiag_coop<8, CR><<<P, CT, 0, st>>>(n, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, cb, kstop);
+        fast ? go(k_tridiag_coop<2, 8, CB, CB, true>, CB) : go(k_tridiag_coop<2, 8, CB, CB>, CB);
+      else if (n <= 2 * CB) go(k_tridiag_coop<2, CR, CB, CB>, CB);
+      else if (n <= 4 * CB) go(k_tridiag_coop<4, CR>, CT);
+      else go(k_tridiag_coop<8, CR>, CT);
       if (hw.block_tri) tridiag_reg(n, kstop, true, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, st);
     } else if (reg_tri) {
       tridiag_reg(n, 0, false, hw.A, ldw, hw.d, hw.e, hw.tau, hw.info, st);
