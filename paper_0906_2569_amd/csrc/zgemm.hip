@@ -79,7 +79,6 @@ constexpr int BN = 64, BK = 16, NT = 256;
 template <typename T, bool CN>
 struct GT {
   static constexpr int BM = (sizeof(T) == 4 && CN) ? 128 : 64;
-  static constexpr int IM = BM / 32;   // 16-row MFMA tiles per wave (two waves along M)
   static constexpr int waves = 3;      // of k_gemm_nn
 };
 
@@ -110,38 +109,47 @@ __device__ __forceinline__ void xcd_block(int& bx, int& by, int& bz) {
 // k_gemm_nn: 2442 against 2477 us for the 200-atom add-back; in float32, and in
 // k_gemm_cn with its transposing writes, slower: 24.4 against 20.5 ms for the
 // 512-atom calbec, 3267 against 2839 us for the float64 200-atom one).
-template <typename T, int BM, bool IL>
+template <typename T, int BM, int BC, bool IL>
 struct Tile {
-  T ar[BK][BM + 1], ai[BK][BM + 1], br[BK][BN + 1], bi[BK][BN + 1];
+  T ar[BK][BM + 1], ai[BK][BM + 1], br[BK][BC + 1], bi[BK][BC + 1];
   __device__ __forceinline__ void put_a(int k, int m, cpx<T> v) { ar[k][m] = v.x; ai[k][m] = v.y; }
   __device__ __forceinline__ void put_b(int k, int n, cpx<T> v) { br[k][n] = v.x; bi[k][n] = v.y; }
   __device__ __forceinline__ cpx<T> get_a(int k, int m) const { return cpx<T>{ar[k][m], ai[k][m]}; }
   __device__ __forceinline__ cpx<T> get_b(int k, int n) const { return cpx<T>{br[k][n], bi[k][n]}; }
 };
-template <typename T, int BM>
-struct Tile<T, BM, true> {
-  cpx<T> a[BK][BM + 1], b[BK][BN + 1];
+template <typename T, int BM, int BC>
+struct Tile<T, BM, BC, true> {
+  cpx<T> a[BK][BM + 1], b[BK][BC + 1];
   __device__ __forceinline__ void put_a(int k, int m, cpx<T> v) { a[k][m] = v; }
   __device__ __forceinline__ void put_b(int k, int n, cpx<T> v) { b[k][n] = v; }
   __device__ __forceinline__ cpx<T> get_a(int k, int m) const { return a[k][m]; }
   __device__ __forceinline__ cpx<T> get_b(int k, int n) const { return b[k][n]; }
 };
 
-// Accumulators of one wave's 32x32 quadrant (2x2 blocks of 16x16): a = t1,
+// The 4 waves' share of a BM x BC output tile: WN waves along N (two, or one
+// for a 16-column tile), 4 / WN along M, each with IM x JN MFMA tiles of 16 x 16.
+template <int BM, int BC>
+struct Part {
+  static constexpr int WN = BC == 16 ? 1 : 2, WM = 4 / WN, IM = BM / (16 * WM), JN = BC / (16 * WN);
+  static __device__ __forceinline__ int row0(int wave) { return (wave % WM) * IM * 16; }
+  static __device__ __forceinline__ int col0(int wave) { return (wave / WM) * JN * 16; }
+};
+
+// Accumulators of one wave's block of IM x JN MFMA tiles: a = t1,
 // b = t2, c = t3 of the three-product form (a = Re C, b = Im C in the
 // four-product form).
 constexpr bool kGauss = true;
 
-template <typename T, int IM>
+template <typename T, int IM, int JN>
 struct CAcc {
   typedef typename Mma<T>::v4 v4;
   static constexpr bool k3 = kGauss;
-  v4 a[IM][2], b[IM][2], c[IM][2];
+  v4 a[IM][JN], b[IM][JN], c[IM][JN];
   __device__ __forceinline__ void zero() {
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) a[i][j] = b[i][j] = c[i][j] = v4{0, 0, 0, 0};
+      for (int j = 0; j < JN; ++j) a[i][j] = b[i][j] = c[i][j] = v4{0, 0, 0, 0};
   }
   __device__ __forceinline__ cpx<T> get(int i, int j, int q) const {
     if constexpr (k3) {
@@ -153,38 +161,39 @@ struct CAcc {
   }
 };
 
-// One BK slice of a BM x 64 tile product held in LDS; each of the 4 waves
-// owns a (BM / 2) x 32 block (IM x 2 MFMA tiles of 16 x 16).
-template <typename T, int BM, bool IL>
-__device__ __forceinline__ void tile_mma(const Tile<T, BM, IL>& t, CAcc<T, BM / 32>& acc, int wm, int wn, int lane) {
-  constexpr int IM = BM / 32, WM = BM / 2;
+// One BK slice of a BM x BC tile product held in LDS
+template <typename T, int BM, int BC, bool IL>
+__device__ __forceinline__ void tile_mma(const Tile<T, BM, BC, IL>& t, CAcc<T, Part<BM, BC>::IM, Part<BM, BC>::JN>& acc,
+                                         int wave, int lane) {
+  constexpr int IM = Part<BM, BC>::IM, JN = Part<BM, BC>::JN;
+  const int rm = Part<BM, BC>::row0(wave), cn = Part<BM, BC>::col0(wave);
   const int r = lane & 15, kq = lane >> 4;
 #pragma unroll
   for (int k4 = 0; k4 < BK; k4 += 4) {
     const int kk = k4 + kq;
-    T ar[IM], ai[IM], br[2], bi[2];
+    T ar[IM], ai[IM], br[JN], bi[JN];
 #pragma unroll
     for (int i = 0; i < IM; ++i) {
-      const cpx<T> v = t.get_a(kk, wm * WM + i * 16 + r);
+      const cpx<T> v = t.get_a(kk, rm + i * 16 + r);
       ar[i] = v.x;
       ai[i] = v.y;
     }
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-      const cpx<T> v = t.get_b(kk, wn * 32 + j * 16 + r);
+    for (int j = 0; j < JN; ++j) {
+      const cpx<T> v = t.get_b(kk, cn + j * 16 + r);
       br[j] = v.x;
       bi[j] = v.y;
     }
-    if constexpr (CAcc<T, IM>::k3) {
-      T sa[IM], sb[2];
+    if constexpr (CAcc<T, IM, JN>::k3) {
+      T sa[IM], sb[JN];
 #pragma unroll
       for (int i = 0; i < IM; ++i) sa[i] = ar[i] + ai[i];
 #pragma unroll
-      for (int j = 0; j < 2; ++j) sb[j] = br[j] + bi[j];
+      for (int j = 0; j < JN; ++j) sb[j] = br[j] + bi[j];
 #pragma unroll
       for (int i = 0; i < IM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < JN; ++j) {
           acc.a[i][j] = Mma<T>::run(ar[i], br[j], acc.a[i][j]);
           acc.b[i][j] = Mma<T>::run(ai[i], bi[j], acc.b[i][j]);
           acc.c[i][j] = Mma<T>::run(sa[i], sb[j], acc.c[i][j]);
@@ -193,7 +202,7 @@ __device__ __forceinline__ void tile_mma(const Tile<T, BM, IL>& t, CAcc<T, BM / 
 #pragma unroll
       for (int i = 0; i < IM; ++i)
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
+        for (int j = 0; j < JN; ++j) {
           acc.a[i][j] = Mma<T>::run(ar[i], br[j], acc.a[i][j]);
           acc.a[i][j] = Mma<T>::run(-ai[i], bi[j], acc.a[i][j]);
           acc.b[i][j] = Mma<T>::run(ar[i], bi[j], acc.b[i][j]);
@@ -206,28 +215,27 @@ __device__ __forceinline__ void tile_mma(const Tile<T, BM, IL>& t, CAcc<T, BM / 
 // partial[z][n][m] = sum_{k in chunk z} conj(A[m*lda + k]) B[n*ldb + k]
 // gridDim.z = 2 nsplit for two products of one launch: z >= nsplit takes B1
 // and writes the partials after those of the first product
-template <typename T, typename TA, typename TB, int BM>
-__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && BM == 64 ? 3 : 2)))
+template <typename T, typename TA, typename TB, int BM, int BC = BN>
+__global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 && BM <= 64 ? 3 : 2)))
 k_gemm_cn(int M, int N, int K, int kchunk, int nsplit, const cpx<TA>* __restrict__ A, int lda,
           const cpx<TB>* __restrict__ B0, const cpx<TB>* __restrict__ B1, int ldb, cpx<T>* __restrict__ P) {
-  constexpr int IM = BM / 32;
-  __shared__ Tile<T, BM, false> t;
+  constexpr int IM = Part<BM, BC>::IM, JN = Part<BM, BC>::JN;
+  __shared__ Tile<T, BM, BC, false> t;
   int bx, by, bz;
   xcd_block<false>(bx, by, bz);   // the output tiles of one K chunk share an XCD
-  const int m0 = bx * BM, n0 = by * BN;
+  const int m0 = bx * BM, n0 = by * BC;
   const int zs = bz % nsplit;
   const cpx<TB>* __restrict__ B = bz >= nsplit ? B1 : B0;
   const int kbeg = zs * kchunk, kend = min(K, kbeg + kchunk);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  CAcc<T, IM> acc;
+  CAcc<T, IM, JN> acc;
   acc.zero();
 
   // Two K slices are in flight in registers while one is multiplied out of
   // LDS: under this kernel's load a fetch takes longer than one slice's
   // products.  Rows past M and columns past N read the last one (their
   // products are not stored), so the loads of a full slice need no checks.
-  constexpr int PA = BM * BK / NT, PB = BN * BK / NT;
+  constexpr int PA = BM * BK / NT, PB = BC * BK / NT;
   const int kk = threadIdx.x % BK;
   const int r0 = threadIdx.x / BK;
   const cpx<TA>* pa[PA];
@@ -273,7 +281,7 @@ k_gemm_cn(int M, int N, int K, int kchunk, int nsplit, const cpx<TA>* __restrict
     }
     __syncthreads();
     if (sl + 2 < nslice) load(xa, xb, sl + 2);
-    tile_mma(t, acc, wm, wn, lane);
+    tile_mma(t, acc, wave, lane);
     __syncthreads();
   };
   if (nslice > 0) load(ra[0], rb[0], 0);
@@ -286,11 +294,11 @@ k_gemm_cn(int M, int N, int K, int kchunk, int nsplit, const cpx<TA>* __restrict
 #pragma unroll
   for (int i = 0; i < IM; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < JN; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int m = m0 + wm * (BM / 2) + i * 16 + mrow<T>(lane, q);
-        const int n = n0 + wn * 32 + j * 16 + mcol(lane);
+        const int m = m0 + Part<BM, BC>::row0(wave) + i * 16 + mrow<T>(lane, q);
+        const int n = n0 + Part<BM, BC>::col0(wave) + j * 16 + mcol(lane);
         if (m < M && n < N) out[(size_t)n * M + m] = acc.get(i, j, q);
       }
 }
@@ -300,7 +308,7 @@ k_gemm_cn(int M, int N, int K, int kchunk, int nsplit, const cpx<TA>* __restrict
 // one launch fill the device better than two launches).
 // SPLIT: the z index is instead the K chunk [z kchunk, (z + 1) kchunk) of the one
 // product (A0), whose partial tile goes to P[z][n][m] unscaled, for k_reduce.
-template <typename T, typename TA, typename TB, bool SPLIT = false>
+template <typename T, typename TA, typename TB, bool SPLIT = false, int BM = GT<T, false>::BM, int BC = BN>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(GT<T, false>::waves)))
 k_gemm_nn(int M, int N, int K, double alpha, const cpx<TA>* __restrict__ A0, const cpx<TA>* __restrict__ A1,
           int lda, const cpx<TB>* __restrict__ B, int ldb, double beta, c128* __restrict__ C0,
@@ -314,17 +322,16 @@ k_gemm_nn(int M, int N, int K, double alpha, const cpx<TA>* __restrict__ A0, con
   c128* __restrict__ C = (!SPLIT && bz) ? C1 : C0;
   const int kbeg = SPLIT ? bz * kchunk : 0;
   const int kend = SPLIT ? min(K, kbeg + kchunk) : K;
-  constexpr int BM = GT<T, false>::BM, IM = GT<T, false>::IM;
-  __shared__ Tile<T, BM, sizeof(T) == 8> t;
-  const int m0 = bx * BM, n0 = by * BN;
+  constexpr int IM = Part<BM, BC>::IM, JN = Part<BM, BC>::JN;
+  __shared__ Tile<T, BM, BC, sizeof(T) == 8> t;
+  const int m0 = bx * BM, n0 = by * BC;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wm = wave & 1, wn = wave >> 1;
-  CAcc<T, IM> acc;
+  CAcc<T, IM, JN> acc;
   acc.zero();
 
   // the next K slice is loaded while the current one is multiplied; rows past
   // M and columns past N read the last one (not stored)
-  constexpr int PA = BM * BK / NT, PB = BN * BK / NT;
+  constexpr int PA = BM * BK / NT, PB = BC * BK / NT;
   const int mi = threadIdx.x % BM, ka = threadIdx.x / BM;   // A: this thread's row, first k
   const int kk = threadIdx.x % BK, nb = threadIdx.x / BK;   // B: its k, first column
   const cpx<TA>* pa = A + (size_t)(kbeg + ka) * lda + min(m0 + mi, M - 1);
@@ -369,7 +376,7 @@ k_gemm_nn(int M, int N, int K, double alpha, const cpx<TA>* __restrict__ A0, con
     }
     __syncthreads();
     if (sl + 1 < nslice) load(sl + 1);
-    tile_mma(t, acc, wm, wn, lane);
+    tile_mma(t, acc, wave, lane);
     __syncthreads();
   }
   if constexpr (SPLIT) {
@@ -377,11 +384,11 @@ k_gemm_nn(int M, int N, int K, double alpha, const cpx<TA>* __restrict__ A0, con
 #pragma unroll
     for (int i = 0; i < IM; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j)
+      for (int j = 0; j < JN; ++j)
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          const int m = m0 + wm * (BM / 2) + i * 16 + mrow<T>(lane, q);
-          const int n = n0 + wn * 32 + j * 16 + mcol(lane);
+          const int m = m0 + Part<BM, BC>::row0(wave) + i * 16 + mrow<T>(lane, q);
+          const int n = n0 + Part<BM, BC>::col0(wave) + j * 16 + mcol(lane);
           if (m < M && n < N) out[(size_t)n * M + m] = acc.get(i, j, q);
         }
     return;
@@ -389,11 +396,11 @@ k_gemm_nn(int M, int N, int K, double alpha, const cpx<TA>* __restrict__ A0, con
 #pragma unroll
   for (int i = 0; i < IM; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j)
+    for (int j = 0; j < JN; ++j)
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
-        const int m = m0 + wm * (BM / 2) + i * 16 + mrow<T>(lane, q);
-        const int n = n0 + wn * 32 + j * 16 + mcol(lane);
+        const int m = m0 + Part<BM, BC>::row0(wave) + i * 16 + mrow<T>(lane, q);
+        const int n = n0 + Part<BM, BC>::col0(wave) + j * 16 + mcol(lane);
         if (m < M && n < N) {
           c128* c = C + (size_t)n * ldc + m;
           const cpx<T> v = acc.get(i, j, q);
@@ -515,6 +522,26 @@ struct Split {
   int nsplit, kchunk;
 };
 
+// Output tile of a product with z planes of workgroups (K chunks or
+// products).  A CU multiplies one 64 x 64 tile's K slice in the time of four
+// 32 x 32 or 64 x 16 ones, and a product with fewer 64 x 64 tiles than CUs
+// leaves the others idle (or multiplies padding, below 64 columns): the small
+// tile is taken where the fullest CU's share is less even at a third more
+// time per product (its operands are read twice as often).  The order of the
+// sums over K does not depend on the tile: the results are the same.
+// Measured, 64 x 64 -> small: 8 atoms, one band, H psi 32.5 -> 24.6 us; phi^H H phi
+// of 64 and 16 columns, K = 949, 20.2 -> 8 us; 64 atoms, 128 bands, float32
+// add-back 78.6 -> 60.2 us (379 tiles on 256 CUs).
+enum TileForm { kTile64, kTile32, kTile16 };
+TileForm tile_form(int M, int N, long z) {
+  constexpr long cus = 256;
+  const long wide = 4 * ceil_div((long)ceil_div(M, 64) * ceil_div(N, 64) * z, cus);
+  const long t32 = ceil_div((long)ceil_div(M, 32) * ceil_div(N, 32) * z, cus);
+  const long t16 = ceil_div((long)ceil_div(M, 64) * ceil_div(N, 16) * z, cus);
+  if (4 * std::min(t32, t16) > 3 * wide) return kTile64;
+  return t16 < t32 || N <= 16 ? kTile16 : kTile32;
+}
+
 // Launch of k_gemm_cn with ns K chunks in all (two products: twice the
 // splits).  The chunks, hence the rounding, are the caller's; the tile height
 // is free.  float32 takes 128 rows unless 64 fill the 256 CUs so much better
@@ -526,15 +553,33 @@ void launch_cn(int M, int N, int K, int kchunk, int nsplit, int ns, const cpx<TA
                const cpx<TB>* B1, int ldb, cpx<T>* P, hipStream_t s) {
   constexpr int cus = 256;
   const int gy = ceil_div(N, BN);
+  auto go = [&](auto kernel, int bm, int bc) {
+    kernel<<<dim3(ceil_div(M, bm), ceil_div(N, bc), ns), NT, 0, s>>>(M, N, K, kchunk, nsplit, A, lda, B0, B1, ldb, P);
+  };
+  const TileForm f = tile_form(M, N, ns);
+  if (f == kTile32) return go(k_gemm_cn<T, TA, TB, 32, 32>, 32, 32);
+  if (f == kTile16) return go(k_gemm_cn<T, TA, TB, 64, 16>, 64, 16);
   if constexpr (GT<T, true>::BM == 128) {
     const long wide = ceil_div((long)ceil_div(M, 128) * gy * ns, cus), half = ceil_div((long)ceil_div(M, 64) * gy * ns, cus);
-    if (100 * 128 * wide <= 106 * 64 * half) {
-      k_gemm_cn<T, TA, TB, 128><<<dim3(ceil_div(M, 128), gy, ns), NT, 0, s>>>(M, N, K, kchunk, nsplit, A, lda, B0, B1,
-                                                                            ldb, P);
-      return;
-    }
+    if (100 * 128 * wide <= 106 * 64 * half) return go(k_gemm_cn<T, TA, TB, 128>, 128, BN);
   }
-  k_gemm_cn<T, TA, TB, 64><<<dim3(ceil_div(M, 64), gy, ns), NT, 0, s>>>(M, N, K, kchunk, nsplit, A, lda, B0, B1, ldb, P);
+  go(k_gemm_cn<T, TA, TB, 64>, 64, BN);
+}
+
+// Launch of k_gemm_nn (SPLIT: z K chunks of one product; else z products)
+template <typename T, typename TA, typename TB, bool SPLIT = false>
+void launch_nn(int z, int M, int N, int K, double alpha, const cpx<TA>* A0, const cpx<TA>* A1, int lda,
+               const cpx<TB>* B, int ldb, double beta, c128* C0, c128* C1, int ldc, const int* guard, hipStream_t s,
+               int kchunk = 0, cpx<T>* P = nullptr, const double* kin = nullptr, const c128* X = nullptr, int ldx = 0) {
+  constexpr int BM = GT<T, false>::BM;
+  auto go = [&](auto kernel, int bm, int bc) {
+    kernel<<<dim3(ceil_div(M, bm), ceil_div(N, bc), z), NT, 0, s>>>(M, N, K, alpha, A0, A1, lda, B, ldb, beta, C0, C1,
+                                                                    ldc, guard, kchunk, P, kin, X, ldx);
+  };
+  const TileForm f = tile_form(M, N, z);
+  if (f == kTile32) return go(k_gemm_nn<T, TA, TB, SPLIT, 32, 32>, 32, 32);
+  if (f == kTile16) return go(k_gemm_nn<T, TA, TB, SPLIT, 64, 16>, 64, 16);
+  go(k_gemm_nn<T, TA, TB, SPLIT>, BM, BN);
 }
 
 Split choose_split(int M, int N, int K, int BM) {
@@ -653,8 +698,7 @@ pw_status pw::zgemm_nn(int M, int N, int K, double alpha, const cpx<TA>* A, int 
                        const int* guard, const double* kin, const c128* X, int ldx) {
   if (M <= 0 || N <= 0) return PW_OK;
   pw::ProfScope ps(pw::PK_GEMM_NN, s, 8.0 * M * N * K);
-  k_gemm_nn<T, TA, TB><<<dim3(ceil_div(M, GT<T, false>::BM), ceil_div(N, BN), 1), NT, 0, s>>>(
-      M, N, K, alpha, A, A, lda, B, ldb, beta, C, C, ldc, guard, 0, nullptr, kin, X, ldx);
+  launch_nn<T>(1, M, N, K, alpha, A, A, lda, B, ldb, beta, C, C, ldc, guard, s, 0, (cpx<T>*)nullptr, kin, X, ldx);
   PW_HIP(hipGetLastError());
   return PW_OK;
 }
@@ -673,8 +717,8 @@ pw_status pw::zgemm_nn_sk(int M, int N, int K, double alpha, const c128* A, int 
   c128* P = static_cast<c128*>(part);
   {
     pw::ProfScope ps(pw::PK_GEMM_NN, s, 8.0 * M * N * K);
-    k_gemm_nn<double, double, double, true><<<dim3(ceil_div(M, GT<double, false>::BM), ceil_div(N, BN), nsplit), NT, 0, s>>>(
-        M, N, K, 1.0, A, A, lda, B, ldb, 0.0, nullptr, nullptr, ldc, nullptr, kchunk, P);
+    launch_nn<double, double, double, true>(nsplit, M, N, K, 1.0, A, A, lda, B, ldb, 0.0, nullptr, nullptr, ldc,
+                                            nullptr, s, kchunk, P);
   }
   {
     pw::ProfScope ps(pw::PK_GEMM_RED, s, (double)nsplit * M * N * sizeof(c128) + 16.0 * M * N);
@@ -690,8 +734,7 @@ pw_status pw::zgemm_nn_pair(int M, int N, int K, const c128* A0, const c128* A1,
                             int ldb, c128* C0, c128* C1, int ldc, hipStream_t s, const int* guard) {
   if (M <= 0 || N <= 0) return PW_OK;
   pw::ProfScope ps(pw::PK_GEMM_NN, s, 16.0 * M * N * K);
-  k_gemm_nn<T, double, double><<<dim3(ceil_div(M, GT<T, false>::BM), ceil_div(N, BN), 2), NT, 0, s>>>(
-      M, N, K, 1.0, A0, A1, lda, B, ldb, 0.0, C0, C1, ldc, guard);
+  launch_nn<T>(2, M, N, K, 1.0, A0, A1, lda, B, ldb, 0.0, C0, C1, ldc, guard, s);
   PW_HIP(hipGetLastError());
   return PW_OK;
 }
