@@ -1268,7 +1268,8 @@ __global__ void __launch_bounds__(NT) k_tridiag_coop(int n, c128* __restrict__ A
 // ---------------------------------------------------------------------------
 // Householder tridiagonalization of a trailing block of at most 96 rows in
 // the registers of one workgroup: 16 x TC threads, thread (tr, tc) holding
-// entries (tr + 16 p, tc + TC q) of the block, p < SR, q < SC.  `base` is the
+// entries (tr + 16 p, tc + TC q) of the block, p < SR, q < SC.  It ends before
+// column `stop` of the block, leaving the rest as it found it.  `base` is the
 // block's first row; with `pending`, reflector base - 1 (stored in A and tau)
 // has still to be applied to it (the state k_tridiag_coop leaves).
 //
@@ -1301,13 +1302,13 @@ __device__ __forceinline__ double row_sum(double v) {
 }
 
 template <int TC, int SR, int SC>
-__global__ void __launch_bounds__(16 * TC) k_tridiag_reg(int n, int base, int pending, c128* __restrict__ A, int ld,
+__global__ void __launch_bounds__(16 * TC) k_tridiag_reg(int n, int base, int pending, int stop, c128* __restrict__ A, int ld,
                                                          double* __restrict__ d, double* __restrict__ e,
                                                          c128* __restrict__ tau, const int* __restrict__ info) {
   if (*info != 0) return;
   static_assert(16 * SR == TC * SC, "square block");
   constexpr int M = 16 * SR, NW = TC / 4;
-  constexpr int V = SC <= 2 ? 4 : 8;   // column sums of a thread (re, then im), padded to a power of two
+  constexpr int V = SC <= 2 ? 4 : SC <= 4 ? 8 : 16;   // column sums of a thread (re, then im), padded to a power of two
   __shared__ c128 s_y[M], s_v[M], s_t;
   __shared__ double s_r[NW];
   const int m = n - base, tid = threadIdx.x, tr = tid & 15, tc = tid >> 4, lane = tid & 63;
@@ -1333,7 +1334,16 @@ __global__ void __launch_bounds__(16 * TC) k_tridiag_reg(int n, int base, int pe
     const int p0 = qc * rows_per;   // rows below 16 p0 are done (compile-time after unrolling)
     for (int cc = 0; cc < TC; ++cc) {
       const int c = qc * TC + cc;
-      if (c >= m) return;   // uniform
+      if (c >= stop) {   // uniform; the rest of the block, reflector c - 1 pending, is the next launch's
+#pragma unroll
+        for (int q = qc; q < SC; ++q)
+#pragma unroll
+          for (int p = p0; p < SR; ++p) {
+            const int i = tr + 16 * p, j = tc + TC * q;
+            if (i >= stop && i < m && j >= stop && j < m) A[(size_t)(base + j) * ld + base + i] = a[p][q];
+          }
+        return;
+      }
       // 1. A v and v^H A v (v is zero above row c)
       double v[V], r = 0.0;
 #pragma unroll
@@ -1421,11 +1431,23 @@ __global__ void __launch_bounds__(16 * TC) k_tridiag_reg(int n, int base, int pe
 // the block [base, n) of at most kRegTridiagN rows
 void tridiag_reg(int n, int base, bool pending, c128* A, int ld, double* d, double* e, c128* tau, const int* info,
                  hipStream_t st) {
-  const int m = n - base, pd = pending ? 1 : 0;
-  if (m <= 32) k_tridiag_reg<16, 2, 2><<<1, 256, 0, st>>>(n, base, pd, A, ld, d, e, tau, info);
-  else if (m <= 48) k_tridiag_reg<16, 3, 3><<<1, 256, 0, st>>>(n, base, pd, A, ld, d, e, tau, info);
-  else if (m <= 64) k_tridiag_reg<16, 4, 4><<<1, 256, 0, st>>>(n, base, pd, A, ld, d, e, tau, info);
-  else k_tridiag_reg<32, 6, 3><<<1, 512, 0, st>>>(n, base, pd, A, ld, d, e, tau, info);
+  auto go = [&](auto kernel, int threads, int stop) {
+    kernel<<<1, threads, 0, st>>>(n, base, pending ? 1 : 0, stop, A, ld, d, e, tau, info);
+  };
+  // One wave per SIMD up to 80 rows (their chain is bound by issue).  96 rows
+  // need two for the registers: 181 us alone, 155 if the last 80 rows, 117 us,
+  // are left to the kernel of one wave
+  if (n - base > 80) {
+    const int stop = n - base - 80;
+    go(k_tridiag_reg<32, 6, 3>, 512, stop);
+    base += stop;
+    pending = true;
+  }
+  const int m = n - base;
+  if (m <= 32) go(k_tridiag_reg<16, 2, 2>, 256, m);
+  else if (m <= 48) go(k_tridiag_reg<16, 3, 3>, 256, m);
+  else if (m <= 64) go(k_tridiag_reg<16, 4, 4>, 256, m);
+  else go(k_tridiag_reg<16, 5, 5>, 256, m);
 }
 
 // ---------------------------------------------------------------------------
