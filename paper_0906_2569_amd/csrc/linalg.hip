@@ -1489,16 +1489,58 @@ __device__ __forceinline__ void sturm_counts(int n, const double* d, const doubl
   }
 }
 
+// The same count from the leading principal minors themselves,
+// p_i = (d_i - x) p_{i-1} - e2_{i-1} p_{i-2} (Givens), whose sign changes it is:
+// one dependent FMA a step where the quotients take a reciprocal (40 against
+// 150 cycles).  Each computed minor is exact for entries changed by a few
+// roundings, as with the quotients.  Every eight steps both minors are scaled
+// by a power of two; eight steps stay in range for |T| up to kMinorMax.  Two
+// successive zeros (a shift that is an eigenvalue of a decoupled leading
+// block, or an underflow) end the recurrence: that shift is counted by
+// quotients.
+constexpr double kMinorMax = 1e30;
+__device__ __forceinline__ int sturm_count_minors(int n, const double* d, const double* e2, double x, double pivmin) {
+  double p0 = 1.0, p1 = d[0] - x;
+  int cnt = (int)((unsigned)__double2hiint(p1) >> 31);
+  bool lost = false;
+  int i = 1;
+  auto step = [&](int j) {
+    const double p2 = fma(d[j] - x, p1, -(e2[j - 1] * p0));
+    cnt += (int)((unsigned)(__double2hiint(p2) ^ __double2hiint(p1)) >> 31);
+    p0 = p1;
+    p1 = p2;
+  };
+  for (; i + 8 <= n; i += 8) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) step(i + j);
+    lost |= p0 == 0.0 && p1 == 0.0;
+    const int ex = -max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+    p0 = __builtin_amdgcn_ldexp(p0, ex);
+    p1 = __builtin_amdgcn_ldexp(p1, ex);
+  }
+  for (; i < n; ++i) step(i);
+  if (lost || (p0 == 0.0 && p1 == 0.0)) {
+    const double xs[1] = {x};
+    int c[1];
+    sturm_counts<1>(n, d, e2, xs, pivmin, c);
+    cnt = c[0];
+  }
+  return cnt;
+}
+
 // One workgroup per wanted eigenvalue k (of 64 or 256 threads: one or four
 // waves, one per SIMD): each round evaluates the Sturm count at NW x 64 x CH
 // equally spaced shifts and keeps the interval between the two shifts that
 // bracket the k-th eigenvalue.
 constexpr int kBisectChains = 2;
+// MINORS: counts by sturm_count_minors, one shift a thread (its chain is short
+// enough that a second one would only wait for issue)
+template <bool MINORS>
 __global__ void __launch_bounds__(256) k_bisect(int n, const double* __restrict__ dg,
                                                 const double* __restrict__ eg, int nev,
                                                 double* __restrict__ w, const int* __restrict__ info) {
   if (*info != 0) return;
-  constexpr int CH = kBisectChains, NS = 64 * CH;
+  constexpr int CH = MINORS ? 1 : kBisectChains, NS = 64 * CH;
   extern __shared__ __align__(16) char smem_raw[];
   double* d = reinterpret_cast<double*>(smem_raw);
   double* e2 = d + n;
@@ -1541,6 +1583,7 @@ __global__ void __launch_bounds__(256) k_bisect(int n, const double* __restrict_
   const int NT = NS * NW;   // shifts per round
   double lo = s_lo, hi = s_hi;
   const double pivmin = s_piv;
+  const bool small = fmax(fabs(lo), fabs(hi)) <= kMinorMax;   // false for NaN
   for (int round = 0; round < 64; ++round) {
     // the same decision in every thread (lo and hi are uniform)
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin) break;
@@ -1549,7 +1592,8 @@ __global__ void __launch_bounds__(256) k_bisect(int n, const double* __restrict_
     int c[CH];
 #pragma unroll
     for (int j = 0; j < CH; ++j) x[j] = lo + step * (NS * wv + CH * lane + j + 1);
-    sturm_counts<CH>(n, d, e2, x, pivmin, c);
+    if (MINORS && small) c[0] = sturm_count_minors(n, d, e2, x[0], pivmin);
+    else sturm_counts<CH>(n, d, e2, x, pivmin, c);
     // first shift (in increasing order) with more than k eigenvalues below it
     int jf = CH;
 #pragma unroll
@@ -2159,7 +2203,11 @@ pw_status pw::heig_solve(HeigWork& hw, int n0, int n, int nev, const c128* H, co
     // four waves per eigenvalue while they find a SIMD each (up to 256
     // eigenvalues); beyond, one wave each (more waves would share SIMDs and
     // the Sturm steps are issue-bound there)
-    k_bisect<<<nev, nev <= 256 ? 256 : 64, sizeof(double) * 2 * n, st>>>(n, hw.d, hw.e, nev, w, hw.info);
+    // (the bare solver keeps the counts by quotients: their rounding reaches its
+    // eigenvectors' signs, see block_tri)
+    const int threads = nev <= 256 ? 256 : 64;
+    if (hw.block_tri) k_bisect<true><<<nev, threads, sizeof(double) * 2 * n, st>>>(n, hw.d, hw.e, nev, w, hw.info);
+    else k_bisect<false><<<nev, threads, sizeof(double) * 2 * n, st>>>(n, hw.d, hw.e, nev, w, hw.info);
   }
   {
     pw::ProfScope ps(pw::PK_INVIT, st);

@@ -54,3 +54,23 @@ def test_real_reduced_problem(ctx, nb):
     plan.close()
     assert st == 0
     np.testing.assert_allclose(eig.cpu().numpy(), w, atol=5e-9, rtol=0)
+
+
+@pytest.mark.parametrize("nb,k", [(7, (0.0, 0.0, 0.0)), (13, (0.0, 0.0, 0.0)), (20, (0.25, 0.1, 0.0))])
+def test_decoupled_blocks(ctx, nb, k):
+    # no potential and no projectors: plane waves as trial vectors give reduced
+    # problems whose tridiagonal has exact zeros and multiple eigenvalues
+    from paper_0906_2569_amd import pwdft
+    p = pwgen.make_cell(8.0, 12.0, 2, nb, 5, kfrac=k, with_vloc=False, with_beta=False)
+    w = oracle.eigh_lowest(oracle.dense_h_of(p), nb)[0]
+    kin = np.real(np.diag(oracle.dense_h_of(p)))
+    order = np.argsort(kin, kind="stable")
+    x0 = np.zeros((nb, p.npw), dtype=np.complex128)
+    x0[np.arange(nb), order[:nb]] = 1.0
+    x0[-1] += 1e-3 * p.psi0[0]     # one of them still to converge
+    plan = pwdft.Plan(ctx, p, nb_max=nb, ndim_max=4)
+    x = torch.from_numpy(x0).cuda()
+    st, eig, resid, _ = plan.davidson(x, opts=pwdft.default_opts(ndim=4, max_iter=400))
+    plan.close()
+    assert st == 0 and resid.max().item() <= 1e-6
+    np.testing.assert_allclose(eig.cpu().numpy(), w, atol=5e-9, rtol=0)
