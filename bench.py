@@ -134,7 +134,7 @@ def roofline(prof, dtype):
 
 FFT_KERNELS = ("k_zinv", "k_plane", "k_zfwd")
 PLANE_FORMS = {0: "one kernel per plane, a quad of lanes per 1D transform", 1: "three kernels",
-               2: "one kernel per plane, 16-lane groups", 3: "one kernel per plane, generic LDS FFT"}
+               2: "one kernel per plane, 16-lane groups", 3: "one kernel per plane, two-step FFT in a wave (float64) or generic LDS FFT"}
 COMPLEX3_KERNELS = ("calbec_gemm", "add_nl_gemm", "zgemm_cn", "zgemm_nn")
 NL_KERNELS = ("calbec_gemm", "add_nl_gemm")
 

@@ -107,8 +107,8 @@ typedef struct {
                                 three-kernel pass); bands are transformed in chunks that fit it;
                                 0 = 2 GiB                                                          */
   int32_t      nl_overlap;   /* projector term of H.psi: 0 = on a side stream beside the transforms
-                                except where a transform workgroup fills a CU's LDS (then after
-                                them on the caller's stream); 1 = always beside; 2 = always after */
+                                except where a transform workgroup fills a CU or a float64 product is
+                                small (then on the caller's stream); 1 = always beside; 2 = never   */
   int32_t      density;      /* 1: also allocate the workspace of pw_density and pw_scf_norm
                                 (the plane copies of the three-kernel pass and one complex grid)   */
   int32_t      gamma;        /* 1: Gamma point with real wavefunctions.  The problem lists the half
@@ -193,7 +193,8 @@ pw_status pw_plan_destroy(pw_plan plan);
 /* Plan sizes: out[0]=npw, out[1]=n_sticks, out[2]=x columns, out[3]=N, out[4]=nbeta,
    out[5]=bands per transform chunk, out[6]/out[7]=form of the float64/float32 plane pass:
    0 register kernel (a quad of lanes per 1D transform), 1 three kernels, 2 lane-group kernel
-   (16 lanes per 1D transform, unpadded plane in LDS), 3 generic LDS kernel; out[7] is 0 for a
+   (16 lanes per 1D transform, unpadded plane in LDS), 3 two-step float64 kernel where it covers
+   the grid, else generic LDS kernel; out[7] is 0 for a
    PW_FP64 plan. */
 pw_status pw_plan_info(pw_plan plan, int64_t out[8]);
 

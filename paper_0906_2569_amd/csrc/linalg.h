@@ -25,7 +25,8 @@ struct HeigWork {
                            // size (half the workgroups of the 8-row form used up to 512 rows):
                            // the form for solves that run concurrently
   bool block_tri = false;  // tridiagonalize trailing blocks of up to 96 rows in one workgroup's
-                           // registers (the Davidson solver).  Off for the bare reduced solver:
+                           // registers, with the short reflector chain, and count eigenvalues
+                           // by minors (the Davidson solver).  Off for the bare reduced solver:
                            // an eigenvector's sign there follows the rounding of the inverse
                            // iteration's shift, so its callers keep the reduction they had
   bool herm_mean = false;  // reduce the Hermitian part of the transformed matrix (the Davidson solver,

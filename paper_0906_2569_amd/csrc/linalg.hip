@@ -1283,10 +1283,10 @@ __global__ void __launch_bounds__(NT) k_tridiag_coop(int n, c128* __restrict__ A
 //      latency of that chain;
 //   3. barrier; every thread reads its entries of the new reflector.
 // Two workgroup barriers and no memory round trip per column: the step is
-// bound by that latency chain (1.2 us a column at 48 rows, 2.0 at 96, where the
-// float64 FMAs of one CU, 12 per entry, add to it).  48 rows 308 -> 56 us and
+// bound by that latency chain (1.1 us a column at 48 rows, 1.5 at 80, 2.5 for the
+// first of 96, where the float64 FMAs of one CU, 12 per entry, add to it).  48 rows 308 -> 56 us and
 // 63 rows 400 -> 82 against k_tridiag, which goes through memory; 64 rows 239
-// -> 83 and 96 rows 385 -> 189 against the cooperative kernel (3.7 us a column).
+// -> 79 and 96 rows 385 -> 160 against the cooperative kernel (3.7 us a column).
 // At 128 rows the entries spill (558 us against 486): larger blocks hand
 // over at 96.
 // ---------------------------------------------------------------------------
@@ -2145,8 +2145,8 @@ pw_status pw::heig_solve(HeigWork& hw, int n0, int n, int nev, const c128* H, co
     pw::ProfScope ps(pw::PK_TRIDIAG, st, 16.0 / 3.0 * n * n * (double)n);
     if (coop_tri) {
       const CoopBuf cb = coop_buf(hw);   // counter and flag cleared by k_isolate
-      // the last kRegTridiagN rows in one workgroup: a column takes 2.0 us
-      // there, 3.7 with a barrier across the device.  The handover leaves
+      // the last kRegTridiagN rows in one workgroup: a column takes 1.7 us
+      // there, 3.7 to 4.2 with a barrier across the device.  The handover leaves
       // reflector kstop - 1 pending, so kstop >= 2
       const int kstop = hw.block_tri ? std::max(2, n - kRegTridiagN) : n + 1;   // n + 1: never
       const bool wide = hw.coop_wide;
