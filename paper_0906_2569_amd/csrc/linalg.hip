@@ -495,7 +495,8 @@ __global__ void __launch_bounds__(256) k_colnorms(int n, int nev, const c128* __
 
 // ---------------------------------------------------------------------------
 // X = L^-H (upper triangular).  One workgroup per column j of Y = L^-1:
-// forward substitution L y = e_j, row by row, then X[j, :] = conj(y)^T.
+// forward substitution L y = e_j, row by row, then X[j, :] = conj(y)^T.  For
+// more than 1024 rows; up to there k_trinv_reg.
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256) k_trinv(int n, const c128* __restrict__ L, int ld,
                                                c128* __restrict__ X, int ldx, const int* __restrict__ info) {
@@ -520,6 +521,50 @@ __global__ void __launch_bounds__(256) k_trinv(int n, const c128* __restrict__ L
   // X[j][i] = conj(Y[i][j]) for i >= j (row j of X), zero for i < j
   for (int i = threadIdx.x; i < n; i += blockDim.x)
     X[(size_t)i * ldx + j] = (i >= j) ? cconj(y[i]) : c128{0.0, 0.0};
+}
+
+// The same for up to NT rows, row tid in a thread's registers.  Bound by the
+// chain from one row to the next, so little is left in it: y_i goes round through
+// one LDS word and one barrier that orders LDS only, and the columns of L are
+// fetched four steps ahead (256 rows: 110 -> 66 us, 1024 rows 1047 -> 574; with
+// several rows a thread it is slower, 8.3 against 3.8 ms at 2048 rows).
+template <int NT>
+__global__ void __launch_bounds__(NT) k_trinv_reg(int n, const c128* __restrict__ L, int ld,
+                                                  c128* __restrict__ X, int ldx, const int* __restrict__ info) {
+  if (*info != 0) return;
+  constexpr int AHEAD = 4;
+  __shared__ c128 s_y[2];   // y_i before its division, by the parity of i
+  const int j = blockIdx.x, k = threadIdx.x;
+  c128 y{k == j ? 1.0 : 0.0, 0.0}, l[AHEAD];
+  double diag[AHEAD];
+  auto fetch = [&](int i, c128& x, double& d) {
+    x = k > i && k < n ? L[(size_t)i * ld + k] : c128{0.0, 0.0};
+    d = L[(size_t)min(i, n - 1) * (ld + 1)].x;
+  };
+  if (k == j) s_y[j & 1] = y;
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) fetch(j + u, l[u], diag[u]);
+  for (int i0 = j; i0 < n; i0 += AHEAD) {
+#pragma unroll
+    for (int u = 0; u < AHEAD; ++u) {
+      const int i = i0 + u;
+      if (i >= n) break;
+      const double inv = 1.0 / diag[u];
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+      __builtin_amdgcn_s_barrier();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+      const c128 v = s_y[i & 1], yi = c128{v.x * inv, v.y * inv};
+      if (k == i) y = yi;
+      if (k > i && k < n) {
+        const c128 t = cmul(l[u], yi);
+        y = c128{y.x - t.x, y.y - t.y};
+        if (k == i + 1) s_y[k & 1] = y;
+      }
+      fetch(i + AHEAD, l[u], diag[u]);
+    }
+  }
+  // X[j][i] = conj(Y[i][j]) for i >= j (row j of X), zero for i < j
+  if (k < n) X[(size_t)k * ldx + j] = k >= j ? cconj(y) : c128{0.0, 0.0};
 }
 
 // ---------------------------------------------------------------------------
@@ -2122,7 +2167,13 @@ pw_status pw::heig_solve(HeigWork& hw, int n0, int n, int nev, const c128* H, co
   if (m > kChRegN) k_rank_check<<<1, 256, 0, st>>>(n, nev, hw.drop, hw.info);   // else done by k_chol_reg
   {
     pw::ProfScope ps(pw::PK_TRINV, st, 8.0 / 3.0 * m * m * (double)m);
-    k_trinv<<<m, 256, sizeof(c128) * m, st>>>(m, L22, ldw, X22, ldw, hw.info);
+    auto go = [&](auto kernel, int threads) { kernel<<<m, threads, 0, st>>>(m, L22, ldw, X22, ldw, hw.info); };
+    if (m <= 64) go(k_trinv_reg<64>, 64);
+    else if (m <= 128) go(k_trinv_reg<128>, 128);
+    else if (m <= 256) go(k_trinv_reg<256>, 256);
+    else if (m <= 512) go(k_trinv_reg<512>, 512);
+    else if (m <= 1024) go(k_trinv_reg<1024>, 1024);
+    else k_trinv<<<m, 256, sizeof(c128) * m, st>>>(m, L22, ldw, X22, ldw, hw.info);
   }
   if (n0 > 0) {
     // X12 = -X11 (U12 X22)
