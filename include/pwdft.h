@@ -124,7 +124,11 @@ typedef struct {
 
 typedef struct {
   int32_t ndim;              /* basis cap = ndim*nb, 2..8 (default 2: the paper's 2N form)          */
-  int32_t max_iter;          /* default 200                                                          */
+  int32_t max_iter;          /* default 200.  With tol_resid < 1e-8 a limit of 200 or more keeps the
+                                plain arithmetic (its rounding decides such a solve, which may use
+                                the limit up with residuals at 1e-9 to 1e-6 Ha); a limit below 200
+                                takes the Hermitian part of the reduced problem, reaches 1e-10 Ha
+                                and rounds differently                                            */
   double  tol_resid;         /* Ha, band converged when ||g_i||_2 <= tol_resid (default 1e-6) ...   */
   double  tol_deig;          /* ... and |eps_i - eps_i(previous)| <= tol_deig (default 5e-9 Ha)     */
   double  precond_floor;     /* Ha, tau of the preconditioner denominator
@@ -159,7 +163,8 @@ typedef struct {
   int32_t n_hpsi_fp64;       /* band-H.psi applications in float64                                   */
   int32_t nconv;             /* converged bands at exit                                              */
   int32_t iters_fp32;        /* iterations done with float32 H.psi (mixed precision)                 */
-  int32_t fresh_starts;      /* rebuilds of the basis with a fresh H.psi (growth budget, ladder)     */
+  int32_t fresh_starts;      /* rebuilds of the basis with a fresh H.psi (growth budget, ladder,
+                                singular overlap)                                                  */
   int32_t nlocked;           /* bands locked when the solve ended (opts.lock)                        */
   double  max_resid;         /* max_i ||g_i||_2 of the final float64 verification                    */
 } pw_david_stats;

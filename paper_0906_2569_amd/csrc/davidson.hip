@@ -388,8 +388,6 @@ pw_status pw::dav_alloc(pw_plan p) {
   void* hwb = nullptr;
   PW_TRY(get(pw::heig_work_bytes((int)nbx), &hwb));
   PW_TRY(pw::heig_setup(W->hw, hwb, (int)nbx));
-  W->hw.block_tri = true;
-  W->hw.herm_mean = true;
   void* hf = nullptr;
   PW_TRY(pw::host_alloc(p, sizeof(DavFlags), &hf));
   W->hflags = static_cast<DavFlags*>(hf);
@@ -429,11 +427,25 @@ constexpr int kStall32 = 12;
 // rotation work (16 npw nb^2 flops) from which sub32 = 1 takes float32 rotations
 constexpr double kSub32MinFlops = 1e11;
 
+// Tolerance below which, and iteration limit from which, a solve keeps the
+// plain arithmetic: the H psi transforms without the two-step kernels, and the
+// reduction without block_tri and herm_mean.  There the residual floor of the
+// plain reduction (1e-9 to 1e-6 Ha in nearly dependent bases) is within reach,
+// and what a solve returns follows every rounding before it: a caller of the
+// default limit gets the bits this arithmetic has always given (8 atoms, 16
+// bands, tolerance 1e-10: 57 of 100 starts converge in 45 to 167 iterations,
+// the rest run to 200 or break down, with a density up to 6e-8 off).  A lower
+// limit does not leave it those iterations, and takes the Hermitian mean (43
+// to 76 iterations in all 100 starts; density within 5e-11).
+constexpr double kPlainTol = 1e-8;
+constexpr int kPlainIters = 200;
+
 struct Solver {
   pw_plan p;
   DavWork& W;
   hipStream_t st;
   pw_david_stats& stats;
+  bool plain;      // see kPlainTol
   int nfact = 0;   // leading basis size whose overlap factor is current
   int nl = 0;      // locked bands: psi[0:nl), hpsi[0:nl), eps[0:nl) stay fixed
   bool sub32 = false;   // Ritz rotations in float32 arithmetic (float32 stage)
@@ -453,7 +465,7 @@ struct Solver {
 
   // H x and, for ultrasoft plans, S x (columns at the same offsets in sphi)
   pw_status hpsi(pw_precision prec, int n, const c128* x, c128* hx, c128* sx = nullptr) {
-    PW_TRY(pw::hpsi_launch(p, prec, n, x, W.ld, hx, W.ld, st));
+    PW_TRY(pw::hpsi_launch(p, prec, n, x, W.ld, hx, W.ld, st, plain));
     if (p->us && sx) PW_TRY(pw::spsi_launch(p, prec, n, x, W.ld, sx, W.ld, st));
     if (prec == PW_FP64) stats.n_hpsi_fp64 += n; else stats.n_hpsi_fp32 += n;
     return PW_OK;
@@ -702,7 +714,8 @@ extern "C" pw_status davidson_solve(pw_plan p, int32_t nb, pw_c128* psi_u, int32
   PW_HIP(hipSetDevice(p->device));
   hipStream_t st = static_cast<hipStream_t>(stream);
   pw_david_stats stats{};
-  Solver S{p, W, st, stats};
+  Solver S{p, W, st, stats, o.tol_resid < kPlainTol && o.max_iter >= kPlainIters};
+  W.hw.block_tri = W.hw.herm_mean = !S.plain;
   const int npw = p->npw;
   pw_precision prec = (p->opts.precision == PW_MIXED) ? PW_MIXED : PW_FP64;
   c128* psi = reinterpret_cast<c128*>(psi_u);
@@ -721,7 +734,7 @@ extern "C" pw_status davidson_solve(pw_plan p, int32_t nb, pw_c128* psi_u, int32
   double amp = 1.0;   // accumulated error growth of the carried-over H phi
   double best32 = INFINITY;   // float32 stage: smallest max ||g_i|| so far ...
   int stall32 = 0;            // ... and iterations since it last halved
-  bool retried = false;
+  bool collapsed = false;   // plain arithmetic: a singular overlap has been met
   pw_status result = PW_OK;
   DavFlags f{};
   for (;;) {
@@ -746,9 +759,17 @@ extern "C" pw_status davidson_solve(pw_plan p, int32_t nb, pw_c128* psi_u, int32
       // the newest corrections made the overlap singular: the Ritz vectors
       // were not replaced; start afresh from them (H psi and the reduced
       // matrices formed anew: what accumulated in the carried ones is part of
-      // the trouble) and go on
-      if (retried || nbase == nb - S.nl) { result = pw::fail(PW_EBREAKDOWN, "reduced overlap matrix not positive definite"); break; }
-      retried = true;
+      // the trouble) and go on.  A block that is singular by itself ends the
+      // solve.
+      if (nbase == nb - S.nl) { result = pw::fail(PW_EBREAKDOWN, "reduced overlap matrix not positive definite"); break; }
+      if (S.plain && !collapsed) {   // the first time, onto the carried H psi
+        collapsed = true;
+        PW_HIP(hipMemsetAsync(W.hw.info, 0, sizeof(int), st));
+        PW_TRY(S.collapse(nb - S.nl));
+        nbase = nb - S.nl;
+        stats.restarts++;
+        continue;
+      }
       PW_HIP(hipMemcpy2DAsync(W.phi, sizeof(c128) * W.ld, W.psi + (size_t)S.nl * W.ld, sizeof(c128) * W.ld,
                               sizeof(c128) * npw, nb - S.nl, hipMemcpyDeviceToDevice, st));
       PW_TRY(S.start_block(prec, nb - S.nl));
@@ -758,7 +779,6 @@ extern "C" pw_status davidson_solve(pw_plan p, int32_t nb, pw_c128* psi_u, int32
       stats.fresh_starts++;
       continue;
     }
-    retried = false;   // this factorization held: a later singular one is collapsed again, not the end
     if (f.nan) { result = pw::fail(PW_ENAN, "non-finite residual norm"); break; }
     if (p->cancel.exchange(0)) { result = pw::fail(PW_ECANCELLED, "solve cancelled (pw_cancel)"); break; }
     if (fp32_stage && f.maxr < kStallZone * o.ladder_switch) {
@@ -820,7 +840,7 @@ extern "C" pw_status davidson_solve(pw_plan p, int32_t nb, pw_c128* psi_u, int32
   // final float64 verification of the output block
   PW_HIP(hipMemcpy2DAsync(psi, sizeof(c128) * ldpsi, W.psi, sizeof(c128) * W.ld, sizeof(c128) * npw, nb,
                           hipMemcpyDeviceToDevice, st));
-  PW_TRY(pw::hpsi_launch(p, PW_FP64, nb, psi, ldpsi, W.hpsi, W.ld, st));
+  PW_TRY(pw::hpsi_launch(p, PW_FP64, nb, psi, ldpsi, W.hpsi, W.ld, st, S.plain));
   if (p->us) PW_TRY(pw::spsi_launch(p, PW_FP64, nb, psi, ldpsi, W.spsi, W.ld, st));
   stats.n_hpsi_fp64 += nb;
   k_final<<<nb, 256, 0, st>>>(npw, psi, ldpsi, W.hpsi, W.ld, eig, resid, p->us ? W.spsi : nullptr, p->gamma ? 1 : 0);

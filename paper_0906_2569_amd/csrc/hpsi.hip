@@ -1002,14 +1002,14 @@ ZFns<T> zreg_kernels(int n3) {
 }
 
 // z passes of the length: the quad form where a quad holds a column in
-// registers, else the 16-lane form, else (float64) the two-step form; inv ==
-// nullptr: the LDS Stockham kernels
+// registers, else the 16-lane form, else (float64, unless `plain`) the two-step
+// form; inv == nullptr: the LDS Stockham kernels
 template <typename T>
-ZFns<T> z_fns(int n3) {
+ZFns<T> z_fns(int n3, bool plain = false) {
   ZFns<T> f = zreg_kernels<T>(n3);
   if (f.inv == nullptr) f = zgrp_kernels<T>(n3);
   if constexpr (sizeof(T) == 8)
-    if (f.inv == nullptr) f = pw::zwave_f64(n3);
+    if (f.inv == nullptr && !plain) f = pw::zwave_f64(n3);
   return f;
 }
 
@@ -1105,11 +1105,12 @@ pw::PlaneWaveShape plane_wave_shape(const pw::PlaneWave<T>& e, int n2, int nxr, 
 enum PlaneForm { kFormQuad = 0, kFormSplit = 1, kFormGroup = 2, kFormLds = 3 };
 
 template <typename T>
-bool plane_form_ok(int form, int n1, int n2, int nxr) {
+bool plane_form_ok(int form, int n1, int n2, int nxr, bool plain = false) {
   switch (form) {
     case kFormQuad: return plane_quad_fits<T>(n1, n2, nxr);
     case kFormGroup: return plane_oct_fits<T>(n1, n2, nxr);
-    case kFormLds: return plane_wave_of<T>(n1, n2, nxr).fn != nullptr || plane_batch<T>(n1, n2, nxr) > 0;
+    case kFormLds:
+      return (!plain && plane_wave_of<T>(n1, n2, nxr).fn != nullptr) || plane_batch<T>(n1, n2, nxr) > 0;
     default: return true;   // three kernels fit any grid the plan accepts
   }
 }
@@ -1121,9 +1122,10 @@ bool plane_form_ok(int form, int n1, int n2, int nxr) {
 // lane-group kernel, else the register kernel with one plane per workgroup,
 // else the generic LDS kernel, else three kernels.  (At 144^2 in float32 the
 // lane-group kernel runs two workgroups per CU where the one-plane register
-// kernel runs one: 12.5 against 18.4 ms per 1024-band H.psi.)
+// kernel runs one: 12.5 against 18.4 ms per 1024-band H.psi.)  plain: without
+// the two-step kernels.
 template <typename T>
-int plane_form_for(int mode, int n1, int n2, int nxr) {
+int plane_form_for(int mode, int n1, int n2, int nxr, bool plain = false) {
   if (mode == 1) return kFormSplit;
   if (mode == 2 && plane_form_ok<T>(kFormGroup, n1, n2, nxr)) return kFormGroup;
   if (mode == 4 && plane_form_ok<T>(kFormQuad, n1, n2, nxr)) return kFormQuad;
@@ -1133,11 +1135,11 @@ int plane_form_for(int mode, int n1, int n2, int nxr) {
   // (74..93), at 60^2 it is level alone (114 against 109) and faster beside
   // the projector products (269 against 287 us a product of 100 bands), at
   // 80^2 to 128^2 (118..138) the lane-group kernel is faster (107..136)
-  if (n1 == n2 && n1 >= 64 && n1 <= 72 && plane_wave_of<T>(n1, n2, nxr).fn != nullptr) return kFormLds;
+  if (!plain && n1 == n2 && n1 >= 64 && n1 <= 72 && plane_wave_of<T>(n1, n2, nxr).fn != nullptr) return kFormLds;
   if (plane_reg_kernel<T, 2>(n1, n2) != nullptr && plane_reg_lds_bytes<T>(n1, nxr, 2) <= kPlaneRegMaxLds)
     return kFormQuad;
   for (int f : {(int)kFormGroup, (int)kFormQuad, (int)kFormLds})
-    if (plane_form_ok<T>(f, n1, n2, nxr)) return f;
+    if (plane_form_ok<T>(f, n1, n2, nxr, plain)) return f;
   return kFormSplit;
 }
 
@@ -1730,11 +1732,18 @@ struct PlaneLaunch {
   size_t pl = 0;                  // its LDS (or that of the three-kernel form)
 };
 
+// plain: in place of the two-step kernels, the form and kernel of the grid
+// without them (where the plan has the workspace that needs)
 template <typename T>
-pw_status plane_setup(pw_plan p, int form, PlaneLaunch<T>& L) {
+pw_status plane_setup(pw_plan p, int form, PlaneLaunch<T>& L, bool plain = false) {
+  const int n1 = p->n1, n2 = p->n2, nxr = p->nxr;
+  if (plain && form == kFormLds && plane_wave_of<T>(n1, n2, nxr).fn != nullptr) {
+    const int f = plane_form_for<T>(p->opts.plane_mode, n1, n2, nxr, true);
+    if (f == kFormSplit && p->rows == nullptr) plain = false;
+    else form = f;
+  }
   L = PlaneLaunch<T>{};
   L.form = form;
-  const int n1 = p->n1, n2 = p->n2, nxr = p->nxr;
   switch (form) {
     case kFormQuad:
       // two z planes per workgroup where their LDS fits (the last passes over
@@ -1758,7 +1767,7 @@ pw_status plane_setup(pw_plan p, int form, PlaneLaunch<T>& L) {
       if (L.olds > 64 * 1024) PW_TRY(raise_lds_limit((const void*)L.poct, (int)L.olds));
       break;
     case kFormLds:
-      L.pwv = plane_wave_of<T>(n1, n2, nxr);
+      if (!plain) L.pwv = plane_wave_of<T>(n1, n2, nxr);
       if (L.pwv.fn != nullptr) {
         PW_TRY(raise_lds_limit((const void*)L.pwv.fn, (int)kPlaneWaveMaxLds));
         break;
@@ -1879,7 +1888,7 @@ pw_status tune_plane(pw_plan p, hipStream_t s) {
 
 template <typename T>
 pw_status hpsi_fft(pw_plan p, int nb, const c128* psi, int ldpsi, c128* hpsi, int ldhpsi,
-                   hipStream_t s, bool accumulate, hipEvent_t join) {
+                   hipStream_t s, bool accumulate, hipEvent_t join, bool plain) {
   const bool f64 = sizeof(T) == 8;
   const SphereMap m = p->map();
   const cpx<T>* tw1 = f64 ? (const cpx<T>*)p->tw64_1 : (const cpx<T>*)p->tw32_1;
@@ -1888,11 +1897,11 @@ pw_status hpsi_fft(pw_plan p, int nb, const c128* psi, int ldpsi, c128* hpsi, in
   const T* vr = f64 ? (const T*)p->vr64 : (const T*)p->vr32;
   PW_CHECK(vr != nullptr, PW_EINVAL, "float32 H.psi needs a PW_MIXED plan");
   PlaneLaunch<T> pln;
-  PW_TRY(plane_setup<T>(p, f64 ? p->form64 : p->form32, pln));
+  PW_TRY(plane_setup<T>(p, f64 ? p->form64 : p->form32, pln, plain));
   const size_t zl = z_lds_bytes<T>(p->n3);
   cpx<T>* st = static_cast<cpx<T>*>(p->sticks);
   const int gz = ceil_div(p->nst, ZSB);
-  const ZFns<T> zr = z_fns<T>(p->n3);
+  const ZFns<T> zr = z_fns<T>(p->n3, plain);
   const int gzr = zr.inv ? ceil_div(p->nst, zr.sticks) : 0;
   // algorithmic bytes per band: sphere in/out (complex128) and one write plus
   // one read of the stick columns per transform direction; V(r) once per pass
@@ -2077,7 +2086,7 @@ bool nl_beside(pw_plan p, bool f64, int nb) {
 }
 
 pw_status pw::hpsi_launch(pw_plan p, pw_precision prec, int nb, const c128* psi, int ldpsi,
-                          c128* hpsi, int ldhpsi, hipStream_t s) {
+                          c128* hpsi, int ldhpsi, hipStream_t s, bool plain) {
   if (nb == 0) return PW_OK;
   const bool f64 = prec == PW_FP64;
   if (!f64) PW_CHECK(p->opts.precision == PW_MIXED, PW_EINVAL, "float32 H.psi needs a PW_MIXED plan");
@@ -2099,8 +2108,8 @@ pw_status pw::hpsi_launch(pw_plan p, pw_precision prec, int nb, const c128* psi,
     PW_HIP(hipEventRecord(p->ev_join, p->side));
     join = p->ev_join;
   }
-  if (f64) PW_TRY(hpsi_fft<double>(p, nb, psi, ldpsi, hpsi, ldhpsi, s, p->nbeta > 0, join));
-  else PW_TRY(hpsi_fft<float>(p, nb, psi, ldpsi, hpsi, ldhpsi, s, p->nbeta > 0, join));
+  if (f64) PW_TRY(hpsi_fft<double>(p, nb, psi, ldpsi, hpsi, ldhpsi, s, p->nbeta > 0, join, plain));
+  else PW_TRY(hpsi_fft<float>(p, nb, psi, ldpsi, hpsi, ldhpsi, s, p->nbeta > 0, join, plain));
   return PW_OK;
 }
 

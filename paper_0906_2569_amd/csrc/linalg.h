@@ -26,11 +26,11 @@ struct HeigWork {
                            // the form for solves that run concurrently
   bool block_tri = false;  // tridiagonalize trailing blocks of up to 96 rows in one workgroup's
                            // registers, with the short reflector chain, and count eigenvalues
-                           // by minors (the Davidson solver).  Off for the bare reduced solver:
+                           // by minors (the Davidson solver, except in plain arithmetic).  Off for the bare reduced solver:
                            // an eigenvector's sign there follows the rounding of the inverse
                            // iteration's shift, so its callers keep the reduction they had
-  bool herm_mean = false;  // reduce the Hermitian part of the transformed matrix (the Davidson solver,
-                           // where its triangles can differ by 1e-11); off for the bare solver as above
+  bool herm_mean = false;  // reduce the Hermitian part of the transformed matrix (the Davidson solver
+                           // as above, where its triangles can differ by 1e-11); off for the bare solver
   int cus = 0;             // compute units of the device (set by heig_setup)
   double drop_tol = 1e-10; // Cholesky pivot, relative to the original diagonal entry, below which
                            // a basis direction counts as dependent (lies, to the accuracy of S,

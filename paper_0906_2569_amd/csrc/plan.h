@@ -169,9 +169,10 @@ pw_status psi_to_rows(pw_plan p, int nt, int nbands, const c128* psi, int ldpsi,
 pw_status psi_to_sticks(pw_plan p, int nt, int nbands, const c128* psi, int ldpsi, hipStream_t stream);
 // raise a kernel's dynamic LDS limit above the default 64 KB (once per kernel and size)
 pw_status raise_lds_limit(const void* fn, int bytes);
-// H.psi for nb bands (nb <= opts.nb_max) on `stream`.
+// H.psi for nb bands (nb <= opts.nb_max) on `stream`.  plain: without the
+// two-step float64 transforms, whose rounding is their own.
 pw_status hpsi_launch(pw_plan p, pw_precision prec, int nb, const c128* psi, int ldpsi,
-                      c128* hpsi, int ldhpsi, hipStream_t stream);
+                      c128* hpsi, int ldhpsi, hipStream_t stream, bool plain = false);
 
 // C[m, n] = alpha sum_k conj(A[k, m]) B[k, n] + beta Cin[m, n]  (A, B K-contiguous columns),
 // C col-major ldc, complex128; Cin = C unless given (col-major, ldcin).
