@@ -16,6 +16,7 @@
 //        (split K, partials summed in a fixed order: deterministic)
 //   nn : C[n*ldc + m] = alpha sum_k A[k*lda + m] B[n*ldb + k] + beta C[n*ldc + m]
 #include <algorithm>
+#include <climits>
 
 #include "plan.h"
 #include "profile.h"
@@ -101,8 +102,9 @@ __device__ __forceinline__ void rtile_mma(const RTile<T>& t, typename RMma<T>::v
   }
 }
 
-// P[z][n][m] = sum_{k in chunk z} A[m*lda + k] B[n*ldb + k]
-template <typename T, typename TA, typename TB>
+// P[z][n][m] = sum_{k in chunk z} A[m*lda + k] B[n*ldb + k].  Off holds the
+// offset of a row within its tile, up to 63 strides (dgemm_tn picks it).
+template <typename T, typename TA, typename TB, typename Off>
 __global__ void __launch_bounds__(NT) __attribute__((amdgpu_waves_per_eu(3)))
 k_dgemm_tn(int M, int N, int K, int kchunk, const TA* __restrict__ A, long lda, const TB* __restrict__ B, long ldb,
            T* __restrict__ P) {
@@ -121,16 +123,16 @@ k_dgemm_tn(int M, int N, int K, int kchunk, const TA* __restrict__ A, long lda, 
     for (int j = 0; j < 2; ++j) c[i][j] = v4{0, 0, 0, 0};
   // the next K slice is loaded while the current one is multiplied; rows past
   // M and columns past N read the last one (not stored), so full slices need no
-  // checks (offsets: a plan's grid bounds npw, 63 lda stays within 32 bits)
+  // checks
   constexpr int PER = BM * BK / NT, RP = NT / BK;
   const int kk = threadIdx.x % BK, r0 = threadIdx.x / BK;
   const TA* a0 = A + (size_t)m0 * lda + kbeg;
   const TB* b0 = B + (size_t)n0 * ldb + kbeg;
-  unsigned oa[PER], ob[PER];
+  Off oa[PER], ob[PER];
 #pragma unroll
   for (int it = 0; it < PER; ++it) {
-    oa[it] = (unsigned)min(r0 + it * RP, M - 1 - m0) * (unsigned)lda + kk;
-    ob[it] = (unsigned)min(r0 + it * RP, N - 1 - n0) * (unsigned)ldb + kk;
+    oa[it] = (Off)min(r0 + it * RP, M - 1 - m0) * (Off)lda + kk;
+    ob[it] = (Off)min(r0 + it * RP, N - 1 - n0) * (Off)ldb + kk;
   }
   const int klen = max(kend - kbeg, 0), nfull = klen / BK, rem = klen % BK, nslice = nfull + (rem ? 1 : 0);
   TA ra[PER];
@@ -315,8 +317,13 @@ pw_status pw::dgemm_tn(int M, int N, int K, const TA* A, long lda, const TB* B, 
   T* P = static_cast<T*>(part);
   {
     pw::ProfScope ps(prof >= 0 ? prof : pw::PK_GEMM_CN, s, 2.0 * M * N * (double)K);
-    k_dgemm_tn<T, TA, TB><<<dim3(ceil_div(M, BM), ceil_div(N, BN), ns), NT, 0, s>>>(M, N, K, kchunk, A, lda, B, ldb,
-                                                                                   P);
+    auto go = [&](auto kernel) {
+      kernel<<<dim3(ceil_div(M, BM), ceil_div(N, BN), ns), NT, 0, s>>>(M, N, K, kchunk, A, lda, B, ldb, P);
+    };
+    // 32-bit row offsets (16 registers fewer) while a tile's rows stay within
+    // them.  A block of bands may have any stride its caller gave it.
+    if ((BM - 1) * std::max(lda, ldb) + BK <= (long)UINT_MAX) go(k_dgemm_tn<T, TA, TB, unsigned>);
+    else go(k_dgemm_tn<T, TA, TB, size_t>);
   }
   const int g = std::min(4096, ceil_div((size_t)M * N, 256));
   k_dreduce<T, TA, TB><<<g, 256, 0, s>>>(M, N, ns, P, A, lda, B, ldb, w0, alpha, beta, C, ldc, cplx_out ? 1 : 0);
