@@ -1341,6 +1341,7 @@ extern "C" size_t pw_footprint_bytes(const pw_problem* pr, const pw_plan_opts* o
   b += (size_t)pr->npw * (4 * sizeof(int) + 2 * sizeof(double));
   b += (size_t)geo.nst * 3 * sizeof(int) + geo.n1 * sizeof(int);
   b += (size_t)geo.nst * geo.n3 * sizeof(int);   // (z, stick) -> sphere map
+  b += (size_t)geo.nxr * geo.n2 * sizeof(int);   // (column, y) -> stick map
   b += N * (sizeof(double) + (mixed ? sizeof(float) : 0));
   b += (size_t)pr->nbeta * ldb * (sizeof(c128) + (mixed ? sizeof(c64) : 0));
   b += (size_t)pr->nbeta * (2 * sizeof(int) + geo.nhmax * (sizeof(c128) + sizeof(c64)));

@@ -91,6 +91,7 @@ struct pw_plan_s {
   int *gpos_p = nullptr, *gpos_m = nullptr;   // Gamma: [npw] stick position of G and of -G
 
   // maps (device)
+  // (cy_st, [nxr][n2]: stick of (x column, y) or -1, for the lane-group and two-step plane kernels)
   int *st_ptr = nullptr, *ent_g = nullptr, *ent_z = nullptr, *ent_s = nullptr, *st_hx = nullptr,
       *st_i2 = nullptr, *i1_hx = nullptr, *zidx = nullptr, *col_ptr = nullptr, *cy_st = nullptr;
   double* kin = nullptr;     // [npw]

@@ -82,6 +82,27 @@ def test_host_side_validation_without_gpu(lib):
     assert lib.pw_footprint_bytes(ctypes.byref(s), ctypes.byref(o)) == 0
 
 
+def test_footprint_counts_the_column_map(lib):
+    # two grids that differ in n2 alone: n1 n3 values of V(r) and, per x column,
+    # an entry of the (column, y) -> stick map more for each y
+    import numpy as np
+    from paper_0906_2569_amd import pwdft, pwgen
+    pwdft.load(LIB)
+    p = pwgen.tiny_cell(3, a=6.5, ecut_ry=6.0, natoms=1, nb=4)
+    s = pwdft.Problem()
+    miller = np.ascontiguousarray(p.miller, dtype=np.int32)
+    kpg = np.ascontiguousarray(p.kpg)
+    s.npw, s.miller, s.kpg, s.vloc_r, s.nbeta = len(miller), miller.ctypes.data, kpg.ctypes.data, 1, 0
+    o = pwdft.PlanOpts(pwdft.PW_FP64, 4, 0)
+    need = {}
+    for n2 in (25, 40):
+        s.nr[0], s.nr[1], s.nr[2] = 30, n2, 27
+        need[n2] = lib.pw_footprint_bytes(ctypes.byref(s), ctypes.byref(o))
+    nxr = len(np.unique(miller[:, 0]))
+    assert need[25] > 0
+    assert need[40] - need[25] == 15 * (8 * 30 * 27 + 4 * nxr)
+
+
 def test_davidson_option_defaults_and_layout(lib):
     # the C defaults land in the binding's fields one for one: a field order
     # or padding that differed between include/pwdft.h and the binding would
