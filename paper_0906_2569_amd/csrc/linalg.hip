@@ -1538,12 +1538,20 @@ __device__ __forceinline__ void sturm_counts(int n, const double* d, const doubl
 // p_i = (d_i - x) p_{i-1} - e2_{i-1} p_{i-2} (Givens), whose sign changes it is:
 // one dependent FMA a step where the quotients take a reciprocal (40 against
 // 150 cycles).  Each computed minor is exact for entries changed by a few
-// roundings, as with the quotients.  Every eight steps both minors are scaled
-// by a power of two; eight steps stay in range for |T| up to kMinorMax.  Two
-// successive zeros (a shift that is an eigenvalue of a decoupled leading
-// block, or an underflow) end the recurrence: that shift is counted by
-// quotients.
-constexpr double kMinorMax = 1e30;
+// roundings, as with the quotients, while the minors stay clear of underflow.
+// Every eight steps both are scaled by a power of two, the larger to [1/2, 1);
+// eight steps from there stay below overflow for |T| up to kMinorMax, and a
+// larger one below 2^-kMinorLost after them (a minor may have met denormals on
+// the way, from which seven steps gain at most (2 kMinorMax)^6), or zero (a
+// shift that is an eigenvalue of a decoupled leading block), ends the
+// recurrence: that shift is counted by quotients.  Below kMinorMin most shifts
+// would.
+constexpr double kMinorMin = 1e-10, kMinorMax = 1e20;
+constexpr int kMinorLost = 600;
+// biased exponent of the larger of |a| and |b| (0: zeros and denormals)
+__device__ __forceinline__ int larger_exponent(double a, double b) {
+  return max(__double2hiint(a) & 0x7fffffff, __double2hiint(b) & 0x7fffffff) >> 20;
+}
 __device__ __forceinline__ int sturm_count_minors(int n, const double* d, const double* e2, double x, double pivmin) {
   double p0 = 1.0, p1 = d[0] - x;
   int cnt = (int)((unsigned)__double2hiint(p1) >> 31);
@@ -1558,13 +1566,13 @@ __device__ __forceinline__ int sturm_count_minors(int n, const double* d, const 
   for (; i + 8 <= n; i += 8) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) step(i + j);
-    lost |= p0 == 0.0 && p1 == 0.0;
-    const int ex = -max(__builtin_amdgcn_frexp_exp(p0), __builtin_amdgcn_frexp_exp(p1));
+    const int ex = 1022 - larger_exponent(p0, p1);
+    lost |= ex > kMinorLost;
     p0 = __builtin_amdgcn_ldexp(p0, ex);
     p1 = __builtin_amdgcn_ldexp(p1, ex);
   }
   for (; i < n; ++i) step(i);
-  if (lost || (p0 == 0.0 && p1 == 0.0)) {
+  if (lost || 1022 - larger_exponent(p0, p1) > kMinorLost) {
     const double xs[1] = {x};
     int c[1];
     sturm_counts<1>(n, d, e2, xs, pivmin, c);
@@ -1628,7 +1636,9 @@ __global__ void __launch_bounds__(256) k_bisect(int n, const double* __restrict_
   const int NT = NS * NW;   // shifts per round
   double lo = s_lo, hi = s_hi;
   const double pivmin = s_piv;
-  const bool small = fmax(fabs(lo), fabs(hi)) <= kMinorMax;   // false for NaN
+  // (a T with a NaN ends in NaN residuals either way; the bounds drop it)
+  const double size = fmax(fabs(lo), fabs(hi));
+  const bool minors = size >= kMinorMin && size <= kMinorMax;
   for (int round = 0; round < 64; ++round) {
     // the same decision in every thread (lo and hi are uniform)
     if (hi - lo <= 2.0 * DBL_EPSILON * fmax(fabs(lo), fabs(hi)) + pivmin) break;
@@ -1637,7 +1647,7 @@ __global__ void __launch_bounds__(256) k_bisect(int n, const double* __restrict_
     int c[CH];
 #pragma unroll
     for (int j = 0; j < CH; ++j) x[j] = lo + step * (NS * wv + CH * lane + j + 1);
-    if (MINORS && small) c[0] = sturm_count_minors(n, d, e2, x[0], pivmin);
+    if (MINORS && minors) c[0] = sturm_count_minors(n, d, e2, x[0], pivmin);
     else sturm_counts<CH>(n, d, e2, x, pivmin, c);
     // first shift (in increasing order) with more than k eigenvalues below it
     int jf = CH;
