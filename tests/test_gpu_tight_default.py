@@ -56,3 +56,15 @@ def test_density_with_a_lower_limit(seed):
     # |delta psi_b| outside the span is at most resid / gap, and the integral of
     # |delta rho| at most 2 sum_b w_b |delta psi_b|
     assert np.abs(rho - ref).sum() <= 2 * 1e-10 / (w[16] - w[15]) * ref.sum()
+
+
+# the overlap turns singular twice: the first time the solve goes on from the
+# carried H psi, the second afresh
+@pytest.mark.parametrize("seed", [11, 26, 55])
+def test_second_singular_overlap(seed):
+    p, st, stats, rho = _solve(seed)
+    assert st == 0
+    assert stats.fresh_starts == 1
+    w, v = oracle.eigh_lowest(oracle.dense_h_of(p), 17)
+    ref = oracle.density(p.miller, p.nr, v[:16], W, 1000.0)
+    assert np.abs(rho - ref).sum() <= 2 * 1e-10 / (w[16] - w[15]) * ref.sum()
