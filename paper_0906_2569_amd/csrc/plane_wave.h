@@ -26,7 +26,7 @@ struct PlaneWaveShape {
   int pp = 0, nwaves = 0;
 };
 
-// fn == nullptr where no kernel covers n1 x n2
+// fn (density) == nullptr where no plane pass (density) kernel covers n1 x n2
 PlaneWave<double> plane_wave_f64(int n1, int n2);
 PlaneWave<double> plane_wave_f64_pairs(int n1, int n2);   // n1 != n2
 

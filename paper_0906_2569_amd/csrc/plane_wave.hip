@@ -6,6 +6,10 @@ pw::PlaneWave<double> pw::plane_wave_f64(int n1, int n2) {
   switch (n1) {
 #define PW_SQUARE(n) \
   case n: return plane_wave_entry<double, n, n>()
+// the density's kernel alone: the register (60) and lane-group (80, 96, 128)
+// kernels are the faster plane pass of H psi there, also when measured
+#define PW_DENSITY(n) \
+  case n: return plane_wave_entry<double, n, n, false>()
     PW_SQUARE(24);
     PW_SQUARE(25);
     PW_SQUARE(27);
@@ -17,21 +21,22 @@ pw::PlaneWave<double> pw::plane_wave_f64(int n1, int n2) {
     PW_SQUARE(48);
     PW_SQUARE(50);
     PW_SQUARE(54);
-    PW_SQUARE(60);
+    PW_DENSITY(60);
     PW_SQUARE(64);
     PW_SQUARE(72);
     PW_SQUARE(75);
-    PW_SQUARE(80);
+    PW_DENSITY(80);
     PW_SQUARE(81);
     PW_SQUARE(90);
-    PW_SQUARE(96);
+    PW_DENSITY(96);
     PW_SQUARE(100);
     PW_SQUARE(108);
     PW_SQUARE(120);
     PW_SQUARE(125);
-    PW_SQUARE(128);
+    PW_DENSITY(128);
     PW_SQUARE(135);
 #undef PW_SQUARE
+#undef PW_DENSITY
     default: return {};
   }
 }

@@ -308,12 +308,12 @@ k_density_wave(SphereMap m, const c128* __restrict__ sticks, int nt, int per, in
     }
 }
 
-template <typename T, int N1, int N2>
+template <typename T, int N1, int N2, bool HPSI = true>
 PlaneWave<T> plane_wave_entry() {
   using X = wavefft::Axis<N1>;
   using Yx = wavefft::Axis<N2>;
   PlaneWave<T> e;
-  e.fn = k_plane_wave<T, N1, N2>;
+  if constexpr (HPSI) e.fn = k_plane_wave<T, N1, N2>;
   e.ys = N2 | 1;
   e.wave_words = X::words > Yx::words ? X::words : Yx::words;
   e.rows = X::RB;

@@ -66,7 +66,6 @@ constexpr int split_a(int n) {
     case 125: return 25;
     case 128: return 16;
     case 135: return 15;
-    case 144: return 12;
     default: return 0;
   }
 }
