@@ -32,6 +32,9 @@ constexpr int plane_wave_points(int n1, int n2) {
 }
 constexpr int plane_wave_threads(int n1, int n2) { return plane_wave_points(n1, n2) <= 10 ? 768 : 512; }
 
+// (see twiddle_powers)
+constexpr bool hold_twiddles(int points) { return points != 10 && points < 25; }
+
 // The planes of one workgroup in LDS: each plane's x columns [nxr][ys], a column of
 // zeros (read where the sphere has no column) and one that takes what is
 // written there.
@@ -73,7 +76,7 @@ __device__ __forceinline__ void inverse_y(const SphereMap& m, const BufView<T>& 
 #pragma unroll
       for (int j = 0; j < Yx::A; ++j) x[r][j] = Yx::used(j) ? st.load(s[j]) : cpx<T>{T(0), T(0)};
       wavefft::WDft<Yx::A, T>::run(x[r], T(1));
-      wavefft::twiddle_powers<Yx::A, T>(x[r], tw2[b]);
+      wavefft::twiddle_powers<Yx::A, hold_twiddles(Yx::A), T>(x[r], tw2, b, false);
     }
     wavefft::exchange_ab<Yx, T>(x, y, W, lane);
 #pragma unroll
@@ -116,7 +119,7 @@ __device__ __forceinline__ void inverse_x_first(const cpx<T>* Y, const PlaneLds&
 #pragma unroll
     for (int j = 0; j < X::A; ++j) x[r][j] = X::used(j) ? yp[off[r][j]] : cpx<T>{T(0), T(0)};
     wavefft::WDft<X::A, T>::run(x[r], T(1));
-    wavefft::twiddle_powers<X::A, T>(x[r], tw1[b]);
+    wavefft::twiddle_powers<X::A, hold_twiddles(X::A), T>(x[r], tw1, b, false);
   }
 }
 
@@ -170,9 +173,7 @@ k_plane_wave(SphereMap m, cpx<T>* __restrict__ sticks, const T* __restrict__ vr,
 #pragma unroll
     for (int r = 0; r < X::R1; ++r) {
       const int id = lane + 64 * r, b = id % X::B, row = q0 + id / X::B;
-      cpx<T> w = tw1[b];
-      w.y = -w.y;
-      wavefft::twiddle_powers<X::A, T>(x[r], w);
+      wavefft::twiddle_powers<X::A, hold_twiddles(X::A), T>(x[r], tw1, b, true);
       wavefft::WDft<X::A, T>::run(x[r], T(-1));
       if (id < X::RB * X::B && row < nrow) {
         const int pz = row / N2;
@@ -200,9 +201,7 @@ k_plane_wave(SphereMap m, cpx<T>* __restrict__ sticks, const T* __restrict__ vr,
 #pragma unroll
     for (int r = 0; r < Yx::R1; ++r) {
       const int id = lane + 64 * r, b = id % Yx::B, c = c0 + id / Yx::B;
-      cpx<T> w = tw2[b];
-      w.y = -w.y;
-      wavefft::twiddle_powers<Yx::A, T>(x[r], w);
+      wavefft::twiddle_powers<Yx::A, hold_twiddles(Yx::A), T>(x[r], tw2, b, true);
       wavefft::WDft<Yx::A, T>::run(x[r], T(-1));
       int s[Yx::A];
       sticks_of<Yx>(m, min(c, ncol - 1), id < Yx::RB * Yx::B && c < ncol, b, s);

@@ -183,24 +183,43 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// x[k] *= w^k, k < A: the even and the odd powers in two chains of w^2 (depth
-// A / 2, so rounding grows half as far as in one chain)
-template <int A, typename T>
-__device__ __forceinline__ void twiddle_powers(cpx<T> (&x)[A], cpx<T> w) {
-  // w is the same in every pass of a caller's loop: keep the compiler from
-  // computing all powers ahead of it (2 A registers held throughout, spilled)
-  asm volatile("" : "+v"(w.x), "+v"(w.y));
-  const cpx<T> w2 = cmul(w, w);
-  cpx<T> we = w2, wo = w;
+// x[k] *= w^k, k < A, w = tw[b] (conjugated where `conj`): w, w^4 and where
+// registers allow w^2 from the table, the other powers as products of those, so
+// that no power is far from the table.  (In one chain of w^2, A / 2 deep, the
+// rounding of V psi was 1.14 to 1.97 times that of the three-kernel plane pass,
+// which reads every power: now 0.82 to 1.02 times on 50^2 to 120^2.)
+//
+// HOLD: w and w^4 stay in registers over the passes of a caller's loop, and the
+// compiler is kept from computing all powers ahead of it (2 A registers, spilled);
+// else the three are read again in each pass.  Held is faster (120^2 Gamma block
+// 7.20 against 7.33 ms) except in steps whose kernels have no registers left: of 10
+// points at three waves per SIMD (50^2 block 112 us held, 100 read again) and of
+// 25 (125^2, 778 and 704).
+template <int A, bool HOLD, typename T>
+__device__ __forceinline__ void twiddle_powers(cpx<T> (&x)[A], const cpx<T>* __restrict__ tw, int b, bool conj) {
+  auto get = [&](int i) {
+    cpx<T> w = tw[i];
+    if (conj) w.y = -w.y;
+    return w;
+  };
+  if constexpr (!HOLD) asm volatile("" : "+v"(b));
+  cpx<T> w1 = get(b), w4 = get(4 * b), w2;
+  if constexpr (HOLD) {
+    asm volatile("" : "+v"(w1.x), "+v"(w1.y), "+v"(w4.x), "+v"(w4.y));
+    w2 = cmul(w1, w1);
+  } else {
+    w2 = get(2 * b);
+  }
+  const cpx<T> w3 = cmul(w1, w2);
+  x[1] = cmul(x[1], w1);
+  x[2] = cmul(x[2], w2);
+  x[3] = cmul(x[3], w3);
+  cpx<T> h = w4;   // w^(4 q)
 #pragma unroll
-  for (int k = 1; k < A; ++k) {
-    if (k & 1) {
-      if (k > 1) wo = cmul(wo, w2);
-      x[k] = cmul(x[k], wo);
-    } else {
-      x[k] = cmul(x[k], we);
-      if (k + 2 < A) we = cmul(we, w2);
-    }
+  for (int k = 4; k < A; ++k) {
+    if (k > 4 && k % 4 == 0) h = cmul(h, w4);
+    const cpx<T> w = k % 4 == 0 ? h : cmul(h, k % 4 == 1 ? w1 : k % 4 == 2 ? w2 : w3);
+    x[k] = cmul(x[k], w);
   }
 }
 

@@ -29,7 +29,7 @@ __device__ __forceinline__ void zinv_tile(const SphereMap& m, int s0, cpx<T>* __
 #pragma unroll
     for (int j = 0; j < X::A; ++j) x[j] = (X::used(j) && s < m.nst) ? load(s, u + X::B * j) : cpx<T>{T(0), T(0)};
     wavefft::WDft<X::A, T>::run(x, T(1));
-    wavefft::twiddle_powers<X::A, T>(x, tw[u]);
+    wavefft::twiddle_powers<X::A, false, T>(x, tw, u, false);
 #pragma unroll
     for (int k = 0; k < X::A; ++k) L[(k * X::B + u) * ZS + sl] = x[k];
   }
@@ -63,9 +63,7 @@ __device__ __forceinline__ void zfwd_tile(const SphereMap& m, int s0, const cpx<
     cpx<T> x[X::A];
 #pragma unroll
     for (int k = 0; k < X::A; ++k) x[k] = L[(k * X::B + u) * ZS + sl];
-    cpx<T> w = tw[u];
-    w.y = -w.y;
-    wavefft::twiddle_powers<X::A, T>(x, w);
+    wavefft::twiddle_powers<X::A, false, T>(x, tw, u, true);
     wavefft::WDft<X::A, T>::run(x, T(-1));
 #pragma unroll
     for (int j = 0; j < X::A; ++j)
