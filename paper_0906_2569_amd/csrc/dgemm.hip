@@ -52,17 +52,19 @@ __device__ __forceinline__ int rrow<double>(int lane, int q) { return 4 * q + (l
 constexpr int BM = 64, BN = 64, BK = 32, NT = 256;
 
 // One K slice in LDS, row k holding its M (N) entries.  Reads take 16
-// neighbouring entries of four rows: rows k and k + 1 lie half the banks
-// apart (float64; a quarter in float32).  Writes take one entry of 32 rows
-// (tn, and B of nn): within a row entry c sits at c ^ s(k), s spreading the
-// rows that share a bank offset over 16 entries.
+// neighbouring entries of four rows, writes one entry of 32 rows (tn, and B of
+// nn).  float64: rows k and k + 1 lie half the banks apart, and within a row
+// entry c sits at c ^ s(k), s spreading the rows that share a bank offset over
+// 16 entries.  float32: rows of odd stride; the same spreading took 20 KB
+// in place of 17 a workgroup and held up the transforms beside it (mixed Gamma
+// products of 140 atoms, 7 bands 178 against 169 us, 4 bands 163 against 160;
+// 200 atoms, 6 bands 230 against 221).
 template <typename T>
 struct RTile {
-  static constexpr int pad = 16;
+  static constexpr bool spread = sizeof(T) == 8;
+  static constexpr int pad = spread ? 16 : 1;
   T a[BK][BM + pad], b[BK][BN + pad];
-  static __device__ __forceinline__ int at(int k, int c) {
-    return c ^ (sizeof(T) == 8 ? (k >> 1) & 15 : ((k >> 2) & 7) << 1);
-  }
+  static __device__ __forceinline__ int at(int k, int c) { return spread ? c ^ ((k >> 1) & 15) : c; }
 };
 
 // workgroups of one output tile range share an XCD (round-robin launch order)
