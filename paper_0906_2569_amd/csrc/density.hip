@@ -222,7 +222,7 @@ extern "C" pw_status pw_density(pw_plan p, int32_t nb, const pw_c128* psi, int32
   // grids of the two-step plane kernels, where the workspace holds a grid of
   // partial sums: the plane stays in LDS and registers (72^3, 128 bands: 1018
   // -> 200 us, 160 of them the plane kernel, bound by its float64 vector work).  Other grids go through the plane copies.
-  const pw::PlaneWave<double> wv = pw::plane_wave_f64(p->n1, p->n2);
+  const pw::PlaneWave wv = pw::plane_wave_f64(p->n1, p->n2);
   const size_t wlds = wv.density ? wv.lds(p->nxr, 1, wv.density_waves) : 0;
   const bool wave = wv.density != nullptr &&
                     (size_t)p->band_chunk * p->n3 * p->n2 * p->nxr * sizeof(c128) >= sizeof(double) * (size_t)p->N;

@@ -1064,9 +1064,9 @@ int plane_batch(int n1, int n2, int nxr) {
 constexpr size_t kPlaneWaveMaxLds = 160 * 1024;
 constexpr int kCus = 256;
 template <typename T>
-pw::PlaneWave<T> plane_wave_of(int n1, int n2, int nxr) {
+pw::PlaneWave plane_wave_of(int n1, int n2, int nxr) {
   if constexpr (sizeof(T) == 8) {
-    const pw::PlaneWave<T> e = pw::plane_wave_f64(n1, n2);
+    const pw::PlaneWave e = pw::plane_wave_f64(n1, n2);
     if (e.fn != nullptr && e.lds(nxr, 1, 2) <= kPlaneWaveMaxLds) return e;
   }
   return {};
@@ -1077,8 +1077,7 @@ pw::PlaneWave<T> plane_wave_of(int n1, int n2, int nxr) {
 // in rounds of nwaves x cols columns (rows); a CU holds as many workgroups as
 // fit its LDS and the waves its registers allow; below 16 waves the latency
 // of one is less and less hidden by the others.
-template <typename T>
-pw::PlaneWaveShape plane_wave_shape(const pw::PlaneWave<T>& e, int n2, int nxr, int pp_only) {
+pw::PlaneWaveShape plane_wave_shape(const pw::PlaneWave& e, int n2, int nxr, int pp_only) {
   pw::PlaneWaveShape best;
   double score = -1.0;
   for (int pp = 1; pp <= (pp_only ? 1 : 6); ++pp)
@@ -1728,7 +1727,7 @@ struct PlaneLaunch {
   size_t plds = 0;
   PlaneOctFn<T> poct = nullptr;   // lane-group kernel
   size_t olds = 0;
-  pw::PlaneWave<T> pwv;           // LDS form on two-step transforms, where it covers the grid ...
+  pw::PlaneWave pwv;              // LDS form on two-step transforms, where it covers the grid ...
   int cb = 0;                     // generic LDS kernel: transforms per batch
   size_t pl = 0;                  // its LDS (or that of the three-kernel form)
 };
@@ -1799,13 +1798,15 @@ void plane_launch(pw_plan p, const PlaneLaunch<T>& L, cpx<T>* st, const T* vr, c
       L.poct<<<dim3(nbc, p->n3), OctCfg<T>::threads, L.olds, s>>>(m, st, vr, tw1);
       break;
     case kFormLds:
-      if (L.pwv.fn != nullptr) {
-        // full workgroups only where there are enough of them
-        pw::PlaneWaveShape sh = plane_wave_shape<T>(L.pwv, p->n2, p->nxr, 0);
-        if ((long)nbc * ceil_div(p->n3, sh.pp) < 2 * kCus) sh = plane_wave_shape<T>(L.pwv, p->n2, p->nxr, 1);
-        const size_t lds = L.pwv.lds(p->nxr, sh.pp, sh.nwaves);
-        L.pwv.fn<<<dim3(nbc, ceil_div(p->n3, sh.pp)), 64 * sh.nwaves, lds, s>>>(m, st, vr, tw1, tw2, sh.pp);
-        break;
+      if constexpr (sizeof(T) == 8) {
+        if (L.pwv.fn != nullptr) {
+          // full workgroups only where there are enough of them
+          pw::PlaneWaveShape sh = plane_wave_shape(L.pwv, p->n2, p->nxr, 0);
+          if ((long)nbc * ceil_div(p->n3, sh.pp) < 2 * kCus) sh = plane_wave_shape(L.pwv, p->n2, p->nxr, 1);
+          const size_t lds = L.pwv.lds(p->nxr, sh.pp, sh.nwaves);
+          L.pwv.fn<<<dim3(nbc, ceil_div(p->n3, sh.pp)), 64 * sh.nwaves, lds, s>>>(m, st, vr, tw1, tw2, sh.pp);
+          break;
+        }
       }
       k_plane<T><<<dim3(nbc, p->n3), PTHREADS, L.pl, s>>>(m, st, vr, tw1, tw2, L.cb);
       break;

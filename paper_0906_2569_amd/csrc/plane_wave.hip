@@ -1,15 +1,15 @@
 // Plane pass on wave-local two-step transforms: square planes.
 #include "plane_wave_impl.h"
 
-pw::PlaneWave<double> pw::plane_wave_f64(int n1, int n2) {
+pw::PlaneWave pw::plane_wave_f64(int n1, int n2) {
   if (n1 != n2) return plane_wave_f64_pairs(n1, n2);
   switch (n1) {
 #define PW_SQUARE(n) \
-  case n: return plane_wave_entry<double, n, n>()
+  case n: return plane_wave_entry<n, n>()
 // the density's kernel alone: the register (60) and lane-group (80, 96, 128)
 // kernels are the faster plane pass of H psi there, also when measured
 #define PW_DENSITY(n) \
-  case n: return plane_wave_entry<double, n, n, false>()
+  case n: return plane_wave_entry<n, n, false>()
     PW_SQUARE(24);
     PW_SQUARE(25);
     PW_SQUARE(27);

@@ -43,10 +43,9 @@ struct PlaneLds {
   __device__ __forceinline__ PlaneLds(int nxr_, int ys_) : nxr(nxr_), ys(ys_), zero(nxr_ * ys_), plane((nxr_ + 2) * ys_) {}
 };
 
-template <typename T>
-__device__ __forceinline__ void clear_zero_columns(cpx<T>* Y, const PlaneLds& L, int np) {
+__device__ __forceinline__ void clear_zero_columns(c128* Y, const PlaneLds& L, int np) {
   for (int i = threadIdx.x; i < np * L.ys; i += blockDim.x)
-    Y[(i / L.ys) * L.plane + L.zero + i % L.ys] = cpx<T>{T(0), T(0)};
+    Y[(i / L.ys) * L.plane + L.zero + i % L.ys] = c128{0.0, 0.0};
 }
 
 // sticks of (column c = pz nxr + x, y = b + B j), or -1
@@ -63,29 +62,29 @@ __device__ __forceinline__ void sticks_of(const SphereMap& m, int c, bool on, in
 }
 
 // inverse y transforms of all ncol columns: sticks -> Y
-template <typename T, class Yx>
-__device__ __forceinline__ void inverse_y(const SphereMap& m, const BufView<T>& st, cpx<T>* Y, T* W, const PlaneLds& L,
-                                          int ncol, const cpx<T>* __restrict__ tw2, int lane, int wave, int nw) {
+template <class Yx>
+__device__ __forceinline__ void inverse_y(const SphereMap& m, const BufView& st, c128* Y, double* W, const PlaneLds& L,
+                                          int ncol, const c128* __restrict__ tw2, int lane, int wave, int nw) {
   for (int c0 = wave * Yx::RB; c0 < ncol; c0 += nw * Yx::RB) {
-    cpx<T> x[Yx::R1][Yx::A], y[Yx::R2][Yx::B];
+    c128 x[Yx::R1][Yx::A], y[Yx::R2][Yx::B];
 #pragma unroll
     for (int r = 0; r < Yx::R1; ++r) {
       const int id = lane + 64 * r, t = id / Yx::B, b = id % Yx::B, c = c0 + t;
       int s[Yx::A];
       sticks_of<Yx>(m, min(c, ncol - 1), id < Yx::RB * Yx::B && c < ncol, b, s);
 #pragma unroll
-      for (int j = 0; j < Yx::A; ++j) x[r][j] = Yx::used(j) ? st.load(s[j]) : cpx<T>{T(0), T(0)};
-      wavefft::WDft<Yx::A, T>::run(x[r], T(1));
-      wavefft::twiddle_powers<Yx::A, hold_twiddles(Yx::A), T>(x[r], tw2, b, false);
+      for (int j = 0; j < Yx::A; ++j) x[r][j] = Yx::used(j) ? st.load(s[j]) : c128{0.0, 0.0};
+      wavefft::WDft<Yx::A>::run(x[r], 1.0);
+      wavefft::twiddle_powers<Yx::A, hold_twiddles(Yx::A)>(x[r], tw2, b, false);
     }
-    wavefft::exchange_ab<Yx, T>(x, y, W, lane);
+    wavefft::exchange_ab<Yx>(x, y, W, lane);
 #pragma unroll
     for (int r = 0; r < Yx::R2; ++r) {
       const int id = lane + 64 * r, t = id / Yx::A, k = id % Yx::A, c = c0 + t;
-      wavefft::WDft<Yx::B, T>::run(y[r], T(1));
+      wavefft::WDft<Yx::B>::run(y[r], 1.0);
       if (id < Yx::RB * Yx::A && c < ncol) {
         const int pz = c / L.nxr;
-        cpx<T>* yc = Y + pz * L.plane + (c - pz * L.nxr) * L.ys + k;
+        c128* yc = Y + pz * L.plane + (c - pz * L.nxr) * L.ys + k;
 #pragma unroll
         for (int q = 0; q < Yx::B; ++q) yc[Yx::A * q] = y[r][q];
       }
@@ -107,26 +106,26 @@ __device__ __forceinline__ void column_offsets(const SphereMap& m, const PlaneLd
 }
 
 // A step of the inverse x transforms of rows q0 .. q0 + RB - 1 (row pz n2 + r), up to the exchange
-template <typename T, class X, int N2>
-__device__ __forceinline__ void inverse_x_first(const cpx<T>* Y, const PlaneLds& L, int q0, int nrow,
-                                                const int (&off)[X::R1][X::A], const cpx<T>* __restrict__ tw1, int lane,
-                                                cpx<T> (&x)[X::R1][X::A]) {
+template <class X, int N2>
+__device__ __forceinline__ void inverse_x_first(const c128* Y, const PlaneLds& L, int q0, int nrow,
+                                                const int (&off)[X::R1][X::A], const c128* __restrict__ tw1, int lane,
+                                                c128 (&x)[X::R1][X::A]) {
 #pragma unroll
   for (int r = 0; r < X::R1; ++r) {
     const int id = lane + 64 * r, b = id % X::B, row = min(q0 + id / X::B, nrow - 1);
     const int pz = row / N2;
-    const cpx<T>* yp = Y + pz * L.plane + (row - pz * N2);
+    const c128* yp = Y + pz * L.plane + (row - pz * N2);
 #pragma unroll
-    for (int j = 0; j < X::A; ++j) x[r][j] = X::used(j) ? yp[off[r][j]] : cpx<T>{T(0), T(0)};
-    wavefft::WDft<X::A, T>::run(x[r], T(1));
-    wavefft::twiddle_powers<X::A, hold_twiddles(X::A), T>(x[r], tw1, b, false);
+    for (int j = 0; j < X::A; ++j) x[r][j] = X::used(j) ? yp[off[r][j]] : c128{0.0, 0.0};
+    wavefft::WDft<X::A>::run(x[r], 1.0);
+    wavefft::twiddle_powers<X::A, hold_twiddles(X::A)>(x[r], tw1, b, false);
   }
 }
 
-template <typename T, int N1, int N2>
+template <int N1, int N2>
 __global__ void __launch_bounds__(plane_wave_threads(N1, N2))
-k_plane_wave(SphereMap m, cpx<T>* __restrict__ sticks, const T* __restrict__ vr, const cpx<T>* __restrict__ tw1,
-             const cpx<T>* __restrict__ tw2, int pp) {
+k_plane_wave(SphereMap m, c128* __restrict__ sticks, const double* __restrict__ vr, const c128* __restrict__ tw1,
+             const c128* __restrict__ tw2, int pp) {
   using X = wavefft::Axis<N1>;
   using Yx = wavefft::Axis<N2>;
   constexpr bool kVAhead = plane_wave_points(N1, N2) > 10 && plane_wave_points(N1, N2) < 25;
@@ -134,50 +133,50 @@ k_plane_wave(SphereMap m, cpx<T>* __restrict__ sticks, const T* __restrict__ vr,
   extern __shared__ __align__(16) char smem_raw[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, nw = blockDim.x >> 6;
   const PlaneLds L(m.nxr, N2 | 1);
-  cpx<T>* Y = reinterpret_cast<cpx<T>*>(smem_raw);   // [pp][nxr + 2][ys]
-  T* W = reinterpret_cast<T*>(Y + pp * L.plane) + wave * WW;
+  c128* Y = reinterpret_cast<c128*>(smem_raw);   // [pp][nxr + 2][ys]
+  double* W = reinterpret_cast<double*>(Y + pp * L.plane) + wave * WW;
   const int z0 = blockIdx.y * pp, band = blockIdx.x;   // band fastest: workgroups in flight share V(r) planes
   const int np = min(pp, m.n3 - z0), ncol = np * m.nxr, nrow = np * N2;
-  const BufView<T> st(sticks + ((size_t)band * m.n3 + z0) * m.ldst, (size_t)np * m.ldst);
+  const BufView st(sticks + ((size_t)band * m.n3 + z0) * m.ldst, (size_t)np * m.ldst);
   clear_zero_columns(Y, L, np);
-  inverse_y<T, Yx>(m, st, Y, W, L, ncol, tw2, lane, wave, nw);
+  inverse_y<Yx>(m, st, Y, W, L, ncol, tw2, lane, wave, nw);
   __syncthreads();
 
   // rows: inverse x, V(r), forward x
   int off[X::R1][X::A];
   column_offsets<X>(m, L, lane, off);
   for (int q0 = wave * X::RB; q0 < nrow; q0 += nw * X::RB) {
-    cpx<T> x[X::R1][X::A], y[X::R2][X::B];
-    T v[X::R2][X::B];   // V(r)
+    c128 x[X::R1][X::A], y[X::R2][X::B];
+    double v[X::R2][X::B];   // V(r)
     auto load_v = [&]() {
 #pragma unroll
       for (int r = 0; r < X::R2; ++r) {
         const int id = lane + 64 * r, row = min(q0 + id / X::A, nrow - 1);
-        const T* vp = vr + ((size_t)z0 * N2 + row) * N1 + id % X::A;
+        const double* vp = vr + ((size_t)z0 * N2 + row) * N1 + id % X::A;
 #pragma unroll
         for (int q = 0; q < X::B; ++q) v[r][q] = vp[X::A * q];
       }
     };
     if constexpr (kVAhead) load_v();
-    inverse_x_first<T, X, N2>(Y, L, q0, nrow, off, tw1, lane, x);
-    wavefft::exchange_ab<X, T>(x, y, W, lane);
+    inverse_x_first<X, N2>(Y, L, q0, nrow, off, tw1, lane, x);
+    wavefft::exchange_ab<X>(x, y, W, lane);
     if constexpr (!kVAhead) load_v();
 #pragma unroll
     for (int r = 0; r < X::R2; ++r) {
-      wavefft::WDft<X::B, T>::run(y[r], T(1));
+      wavefft::WDft<X::B>::run(y[r], 1.0);
 #pragma unroll
       for (int q = 0; q < X::B; ++q) y[r][q] = y[r][q] * v[r][q];
-      wavefft::WDft<X::B, T>::run(y[r], T(-1));
+      wavefft::WDft<X::B>::run(y[r], -1.0);
     }
-    wavefft::exchange_ba<X, T>(y, x, W, lane);
+    wavefft::exchange_ba<X>(y, x, W, lane);
 #pragma unroll
     for (int r = 0; r < X::R1; ++r) {
       const int id = lane + 64 * r, b = id % X::B, row = q0 + id / X::B;
-      wavefft::twiddle_powers<X::A, hold_twiddles(X::A), T>(x[r], tw1, b, true);
-      wavefft::WDft<X::A, T>::run(x[r], T(-1));
+      wavefft::twiddle_powers<X::A, hold_twiddles(X::A)>(x[r], tw1, b, true);
+      wavefft::WDft<X::A>::run(x[r], -1.0);
       if (id < X::RB * X::B && row < nrow) {
         const int pz = row / N2;
-        cpx<T>* yp = Y + pz * L.plane + (row - pz * N2);
+        c128* yp = Y + pz * L.plane + (row - pz * N2);
 #pragma unroll
         for (int j = 0; j < X::A; ++j)
           if (X::used(j)) yp[off[r][j] == L.zero ? L.zero + L.ys : off[r][j]] = x[r][j];
@@ -188,21 +187,21 @@ k_plane_wave(SphereMap m, cpx<T>* __restrict__ sticks, const T* __restrict__ vr,
 
   // forward y: only the stick positions are written
   for (int c0 = wave * Yx::RB; c0 < ncol; c0 += nw * Yx::RB) {
-    cpx<T> x[Yx::R1][Yx::A], y[Yx::R2][Yx::B];
+    c128 x[Yx::R1][Yx::A], y[Yx::R2][Yx::B];
 #pragma unroll
     for (int r = 0; r < Yx::R2; ++r) {
       const int id = lane + 64 * r, k = id % Yx::A, c = min(c0 + id / Yx::A, ncol - 1), pz = c / L.nxr;
-      const cpx<T>* yc = Y + pz * L.plane + (c - pz * L.nxr) * L.ys + k;
+      const c128* yc = Y + pz * L.plane + (c - pz * L.nxr) * L.ys + k;
 #pragma unroll
       for (int q = 0; q < Yx::B; ++q) y[r][q] = yc[Yx::A * q];
-      wavefft::WDft<Yx::B, T>::run(y[r], T(-1));
+      wavefft::WDft<Yx::B>::run(y[r], -1.0);
     }
-    wavefft::exchange_ba<Yx, T>(y, x, W, lane);
+    wavefft::exchange_ba<Yx>(y, x, W, lane);
 #pragma unroll
     for (int r = 0; r < Yx::R1; ++r) {
       const int id = lane + 64 * r, b = id % Yx::B, c = c0 + id / Yx::B;
-      wavefft::twiddle_powers<Yx::A, hold_twiddles(Yx::A), T>(x[r], tw2, b, true);
-      wavefft::WDft<Yx::A, T>::run(x[r], T(-1));
+      wavefft::twiddle_powers<Yx::A, hold_twiddles(Yx::A)>(x[r], tw2, b, true);
+      wavefft::WDft<Yx::A>::run(x[r], -1.0);
       int s[Yx::A];
       sticks_of<Yx>(m, min(c, ncol - 1), id < Yx::RB * Yx::B && c < ncol, b, s);
 #pragma unroll
@@ -273,22 +272,22 @@ k_density_wave(SphereMap m, const c128* __restrict__ sticks, int nt, int per, in
 #pragma unroll
       for (int q = 0; q < X::B; ++q) acc[i][r][q] = 0.0;
   for (int t = t0; t < t1; ++t) {
-    const BufView<double> st(sticks + ((size_t)t * m.n3 + z) * m.ldst, (size_t)m.ldst);
+    const BufView st(sticks + ((size_t)t * m.n3 + z) * m.ldst, (size_t)m.ldst);
     const double wa = gamma ? w[2 * t] : w[t];
     const double wi = gamma ? (2 * t + 1 < nbands ? w[2 * t + 1] : 0.0) : wa;
     __syncthreads();   // the rows of the transform before have been read
-    inverse_y<double, Yx>(m, st, Y, W, L, m.nxr, tw2, lane, wave, nw);
+    inverse_y<Yx>(m, st, Y, W, L, m.nxr, tw2, lane, wave, nw);
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < RR; ++i) {
       const int q0 = (wave + i * nw) * X::RB;
       if (q0 >= N2) break;   // uniform in the wave
       c128 x[X::R1][X::A], y[X::R2][X::B];
-      inverse_x_first<double, X, N2>(Y, L, q0, N2, off, tw1, lane, x);
-      wavefft::exchange_ab<X, double>(x, y, W, lane);
+      inverse_x_first<X, N2>(Y, L, q0, N2, off, tw1, lane, x);
+      wavefft::exchange_ab<X>(x, y, W, lane);
 #pragma unroll
       for (int r = 0; r < X::R2; ++r) {
-        wavefft::WDft<X::B, double>::run(y[r], 1.0);
+        wavefft::WDft<X::B>::run(y[r], 1.0);
 #pragma unroll
         for (int q = 0; q < X::B; ++q) acc[i][r][q] += wa * (y[r][q].x * y[r][q].x) + wi * (y[r][q].y * y[r][q].y);
       }
@@ -307,23 +306,21 @@ k_density_wave(SphereMap m, const c128* __restrict__ sticks, int nt, int per, in
     }
 }
 
-template <typename T, int N1, int N2, bool HPSI = true>
-PlaneWave<T> plane_wave_entry() {
+template <int N1, int N2, bool HPSI = true>
+PlaneWave plane_wave_entry() {
   using X = wavefft::Axis<N1>;
   using Yx = wavefft::Axis<N2>;
-  PlaneWave<T> e;
-  if constexpr (HPSI) e.fn = k_plane_wave<T, N1, N2>;
+  PlaneWave e;
+  if constexpr (HPSI) e.fn = k_plane_wave<N1, N2>;
   e.ys = N2 | 1;
   e.wave_words = X::words > Yx::words ? X::words : Yx::words;
   e.rows = X::RB;
   e.cols = Yx::RB;
   e.max_waves = plane_wave_threads(N1, N2) / 64;
-  if constexpr (sizeof(T) == 8) {
-    constexpr DensityShape ds = density_shape<N1, N2>();
-    if constexpr (ds.waves > 0) {
-      e.density = k_density_wave<N1, N2, ds.rounds>;
-      e.density_waves = ds.waves;
-    }
+  constexpr DensityShape ds = density_shape<N1, N2>();
+  if constexpr (ds.waves > 0) {
+    e.density = k_density_wave<N1, N2, ds.rounds>;
+    e.density_waves = ds.waves;
   }
   return e;
 }

@@ -3,10 +3,10 @@
 // n >= 4 h + 1 for h and h + 1, as a shifted k-point gives them).
 #include "plane_wave_impl.h"
 
-pw::PlaneWave<double> pw::plane_wave_f64_pairs(int n1, int n2) {
+pw::PlaneWave pw::plane_wave_f64_pairs(int n1, int n2) {
 #define PW_PAIR(a, b)                                              \
-  if (n1 == a && n2 == b) return plane_wave_entry<double, a, b>(); \
-  if (n1 == b && n2 == a) return plane_wave_entry<double, b, a>();
+  if (n1 == a && n2 == b) return plane_wave_entry<a, b>(); \
+  if (n1 == b && n2 == a) return plane_wave_entry<b, a>();
   PW_PAIR(24, 25)
   PW_PAIR(25, 30)
   PW_PAIR(30, 36)

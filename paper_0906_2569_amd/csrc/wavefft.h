@@ -17,22 +17,16 @@
 // Range-checked view of n complex values: a load at index -1 (any index past
 // the end) gives zero, a store there is dropped, by the buffer unit's own
 // bounds check, so gathers and scatters through index maps need no branches.
-template <typename T>
 struct BufView {
   __amdgpu_buffer_rsrc_t r;
-  typedef unsigned int word __attribute__((ext_vector_type(sizeof(cpx<T>) / 4)));
-  __device__ __forceinline__ BufView(const cpx<T>* p, size_t n)
-      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<cpx<T>*>(p), 0, (int)(unsigned)(n * sizeof(cpx<T>)), 0x00027000)) {}
-  __device__ __forceinline__ cpx<T> load(int i) const {
-    word v;
-    if constexpr (sizeof(T) == 8) v = __builtin_amdgcn_raw_buffer_load_b128(r, i * 16, 0, 0);
-    else v = __builtin_amdgcn_raw_buffer_load_b64(r, i * 8, 0, 0);
-    return __builtin_bit_cast(cpx<T>, v);
+  typedef unsigned int word __attribute__((ext_vector_type(4)));
+  __device__ __forceinline__ BufView(const c128* p, size_t n)
+      : r(__builtin_amdgcn_make_buffer_rsrc(const_cast<c128*>(p), 0, (int)(unsigned)(n * sizeof(c128)), 0x00027000)) {}
+  __device__ __forceinline__ c128 load(int i) const {
+    return __builtin_bit_cast(c128, __builtin_amdgcn_raw_buffer_load_b128(r, i * 16, 0, 0));
   }
-  __device__ __forceinline__ void store(int i, cpx<T> x) const {
-    const word v = __builtin_bit_cast(word, x);
-    if constexpr (sizeof(T) == 8) __builtin_amdgcn_raw_buffer_store_b128(v, r, i * 16, 0, 0);
-    else __builtin_amdgcn_raw_buffer_store_b64(v, r, i * 8, 0, 0);
+  __device__ __forceinline__ void store(int i, c128 x) const {
+    __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(word, x), r, i * 16, 0, 0);
   }
 };
 
@@ -119,57 +113,57 @@ constexpr int inv_mod(int a, int m) {
   return m == 1 ? 0 : -1;
 }
 
-template <int N, typename T, int F = coprime_factor<N>()>
+template <int N, int F = coprime_factor<N>()>
 struct WDft {
-  static __device__ __forceinline__ void run(cpx<T>* x, T s) {
+  static __device__ __forceinline__ void run(c128* x, double s) {
     constexpr int N1 = F, N2 = N / F;
     constexpr int e1 = N2 * inv_mod(N2 % N1, N1), e2 = N1 * inv_mod(N1 % N2, N2);   // 1 mod N1 (N2), 0 mod the other
-    cpx<T> a[N];
+    c128 a[N];
 #pragma unroll
     for (int n2 = 0; n2 < N2; ++n2) {
-      cpx<T> t[N1];
+      c128 t[N1];
 #pragma unroll
       for (int n1 = 0; n1 < N1; ++n1) t[n1] = x[(N2 * n1 + N1 * n2) % N];
-      WDft<N1, T>::run(t, s);
+      WDft<N1>::run(t, s);
 #pragma unroll
       for (int k1 = 0; k1 < N1; ++k1) a[n2 * N1 + k1] = t[k1];
     }
 #pragma unroll
     for (int k1 = 0; k1 < N1; ++k1) {
-      cpx<T> t[N2];
+      c128 t[N2];
 #pragma unroll
       for (int n2 = 0; n2 < N2; ++n2) t[n2] = a[n2 * N1 + k1];
-      WDft<N2, T>::run(t, s);
+      WDft<N2>::run(t, s);
 #pragma unroll
       for (int k2 = 0; k2 < N2; ++k2) x[(e1 * k1 + e2 * k2) % N] = t[k2];
     }
   }
 };
-template <int N, typename T>
-struct WDft<N, T, 0> {
-  static __device__ __forceinline__ void run(cpx<T>* x, T s) { regfft::RDft<N, T>::run(x, s); }
+template <int N>
+struct WDft<N, 0> {
+  static __device__ __forceinline__ void run(c128* x, double s) { regfft::RDft<N, double>::run(x, s); }
 };
-template <typename T>
-struct WDft<8, T, 0> {
-  static __device__ __forceinline__ void run(cpx<T>* x, T s) { Dft<8, T>::run(x, s); }
+template <>
+struct WDft<8, 0> {
+  static __device__ __forceinline__ void run(c128* x, double s) { Dft<8, double>::run(x, s); }
 };
 // 16 = 2 x 8: the odd half's twiddles are the only products besides Dft<8>'s
-template <typename T>
-struct WDft<16, T, 0> {
-  static __device__ __forceinline__ void run(cpx<T>* x, T s) {
-    cpx<T> e[8], o[8];
+template <>
+struct WDft<16, 0> {
+  static __device__ __forceinline__ void run(c128* x, double s) {
+    c128 e[8], o[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) {
       e[i] = x[2 * i];
       o[i] = x[2 * i + 1];
     }
-    Dft<8, T>::run(e, s);
-    Dft<8, T>::run(o, s);
+    Dft<8, double>::run(e, s);
+    Dft<8, double>::run(o, s);
 #pragma unroll
     for (int k = 0; k < 8; ++k) {
-      cpx<T> v = o[k];
+      c128 v = o[k];
       if (k == 4) v = mul_is(v, s);
-      else if (k != 0) v = cmul(v, cpx<T>{(T)croot::RootTab<16>::v.c[k], s * (T)croot::RootTab<16>::v.s[k]});
+      else if (k != 0) v = cmul(v, c128{croot::RootTab<16>::v.c[k], s * croot::RootTab<16>::v.s[k]});
       x[k] = e[k] + v;
       x[k + 8] = e[k] - v;
     }
@@ -195,37 +189,37 @@ __device__ __forceinline__ void wave_sync() {
 // 7.20 against 7.33 ms) except in steps whose kernels have no registers left: of 10
 // points at three waves per SIMD (50^2 block 112 us held, 100 read again) and of
 // 25 (125^2, 778 and 704).
-template <int A, bool HOLD, typename T>
-__device__ __forceinline__ void twiddle_powers(cpx<T> (&x)[A], const cpx<T>* __restrict__ tw, int b, bool conj) {
+template <int A, bool HOLD>
+__device__ __forceinline__ void twiddle_powers(c128 (&x)[A], const c128* __restrict__ tw, int b, bool conj) {
   auto get = [&](int i) {
-    cpx<T> w = tw[i];
+    c128 w = tw[i];
     if (conj) w.y = -w.y;
     return w;
   };
   if constexpr (!HOLD) asm volatile("" : "+v"(b));
-  cpx<T> w1 = get(b), w4 = get(4 * b), w2;
+  c128 w1 = get(b), w4 = get(4 * b), w2;
   if constexpr (HOLD) {
     asm volatile("" : "+v"(w1.x), "+v"(w1.y), "+v"(w4.x), "+v"(w4.y));
     w2 = cmul(w1, w1);
   } else {
     w2 = get(2 * b);
   }
-  const cpx<T> w3 = cmul(w1, w2);
+  const c128 w3 = cmul(w1, w2);
   x[1] = cmul(x[1], w1);
   x[2] = cmul(x[2], w2);
   x[3] = cmul(x[3], w3);
-  cpx<T> h = w4;   // w^(4 q)
+  c128 h = w4;   // w^(4 q)
 #pragma unroll
   for (int k = 4; k < A; ++k) {
     if (k > 4 && k % 4 == 0) h = cmul(h, w4);
-    const cpx<T> w = k % 4 == 0 ? h : cmul(h, k % 4 == 1 ? w1 : k % 4 == 2 ? w2 : w3);
+    const c128 w = k % 4 == 0 ? h : cmul(h, k % 4 == 1 ? w1 : k % 4 == 2 ? w2 : w3);
     x[k] = cmul(x[k], w);
   }
 }
 
 // A side -> B side: lane (t, b) holds x[.][k], lane (t, k) receives y[.][b]
-template <class X, typename T>
-__device__ __forceinline__ void exchange_ab(const cpx<T> (&x)[X::R1][X::A], cpx<T> (&y)[X::R2][X::B], T* W, int lane) {
+template <class X>
+__device__ __forceinline__ void exchange_ab(const c128 (&x)[X::R1][X::A], c128 (&y)[X::R2][X::B], double* W, int lane) {
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
 #pragma unroll
@@ -250,8 +244,8 @@ __device__ __forceinline__ void exchange_ab(const cpx<T> (&x)[X::R1][X::A], cpx<
 }
 
 // B side -> A side: lane (t, k) holds y[.][b], lane (t, b) receives x[.][k]
-template <class X, typename T>
-__device__ __forceinline__ void exchange_ba(const cpx<T> (&y)[X::R2][X::B], cpx<T> (&x)[X::R1][X::A], T* W, int lane) {
+template <class X>
+__device__ __forceinline__ void exchange_ba(const c128 (&y)[X::R2][X::B], c128 (&x)[X::R1][X::A], double* W, int lane) {
 #pragma unroll
   for (int part = 0; part < 2; ++part) {
 #pragma unroll

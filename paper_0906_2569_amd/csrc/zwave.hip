@@ -19,86 +19,86 @@ template <int N>
 constexpr int zthreads() { return ZS * (wavefft::Axis<N>::A > wavefft::Axis<N>::B ? wavefft::Axis<N>::A : wavefft::Axis<N>::B); }
 
 // inverse transform of the columns x[] that `load(s, z)` gives, into out
-template <typename T, int N, class Load>
-__device__ __forceinline__ void zinv_tile(const SphereMap& m, int s0, cpx<T>* __restrict__ out,
-                                          const cpx<T>* __restrict__ tw, cpx<T>* L, Load load) {
+template <int N, class Load>
+__device__ __forceinline__ void zinv_tile(const SphereMap& m, int s0, c128* __restrict__ out,
+                                          const c128* __restrict__ tw, c128* L, Load load) {
   using X = wavefft::Axis<N>;
   const int sl = threadIdx.x % ZS, u = threadIdx.x / ZS, s = s0 + sl;
   if (u < X::B) {
-    cpx<T> x[X::A];
+    c128 x[X::A];
 #pragma unroll
-    for (int j = 0; j < X::A; ++j) x[j] = (X::used(j) && s < m.nst) ? load(s, u + X::B * j) : cpx<T>{T(0), T(0)};
-    wavefft::WDft<X::A, T>::run(x, T(1));
-    wavefft::twiddle_powers<X::A, false, T>(x, tw, u, false);
+    for (int j = 0; j < X::A; ++j) x[j] = (X::used(j) && s < m.nst) ? load(s, u + X::B * j) : c128{0.0, 0.0};
+    wavefft::WDft<X::A>::run(x, 1.0);
+    wavefft::twiddle_powers<X::A, false>(x, tw, u, false);
 #pragma unroll
     for (int k = 0; k < X::A; ++k) L[(k * X::B + u) * ZS + sl] = x[k];
   }
   __syncthreads();
   if (u < X::A && s < m.nst) {
-    cpx<T> y[X::B];
+    c128 y[X::B];
 #pragma unroll
     for (int b = 0; b < X::B; ++b) y[b] = L[(u * X::B + b) * ZS + sl];
-    wavefft::WDft<X::B, T>::run(y, T(1));
+    wavefft::WDft<X::B>::run(y, 1.0);
 #pragma unroll
     for (int q = 0; q < X::B; ++q) out[(size_t)(u + X::A * q) * m.ldst + s] = y[q];
   }
 }
 
 // forward transform of the columns of `in`; store(s, z, v) takes the positions the sphere can reach
-template <typename T, int N, class Store>
-__device__ __forceinline__ void zfwd_tile(const SphereMap& m, int s0, const cpx<T>* in, const cpx<T>* __restrict__ tw,
-                                          cpx<T>* L, Store store) {
+template <int N, class Store>
+__device__ __forceinline__ void zfwd_tile(const SphereMap& m, int s0, const c128* in, const c128* __restrict__ tw,
+                                          c128* L, Store store) {
   using X = wavefft::Axis<N>;
   const int sl = threadIdx.x % ZS, u = threadIdx.x / ZS, s = s0 + sl;
   if (u < X::A) {
-    cpx<T> y[X::B];
+    c128 y[X::B];
 #pragma unroll
-    for (int q = 0; q < X::B; ++q) y[q] = s < m.nst ? in[(size_t)(u + X::A * q) * m.ldst + s] : cpx<T>{T(0), T(0)};
-    wavefft::WDft<X::B, T>::run(y, T(-1));
+    for (int q = 0; q < X::B; ++q) y[q] = s < m.nst ? in[(size_t)(u + X::A * q) * m.ldst + s] : c128{0.0, 0.0};
+    wavefft::WDft<X::B>::run(y, -1.0);
 #pragma unroll
     for (int b = 0; b < X::B; ++b) L[(u * X::B + b) * ZS + sl] = y[b];
   }
   __syncthreads();
   if (u < X::B && s < m.nst) {
-    cpx<T> x[X::A];
+    c128 x[X::A];
 #pragma unroll
     for (int k = 0; k < X::A; ++k) x[k] = L[(k * X::B + u) * ZS + sl];
-    wavefft::twiddle_powers<X::A, false, T>(x, tw, u, true);
-    wavefft::WDft<X::A, T>::run(x, T(-1));
+    wavefft::twiddle_powers<X::A, false>(x, tw, u, true);
+    wavefft::WDft<X::A>::run(x, -1.0);
 #pragma unroll
     for (int j = 0; j < X::A; ++j)
       if (X::used(j)) store(s, u + X::B * j, x[j]);
   }
 }
 
-template <typename T, int N>
+template <int N>
 __global__ void __launch_bounds__(zthreads<N>())
-k_zinv_wave(SphereMap m, const c128* __restrict__ psi, int ldpsi, cpx<T>* __restrict__ sticks,
-            const cpx<T>* __restrict__ tw, int gz, int nb) {
-  __shared__ cpx<T> L[N * ZS];
+k_zinv_wave(SphereMap m, const c128* __restrict__ psi, int ldpsi, c128* __restrict__ sticks,
+            const c128* __restrict__ tw, int gz, int nb) {
+  __shared__ c128 L[N * ZS];
   int chunk, band;
   if (!pw::z_tile(gz, nb, chunk, band)) return;
   const c128* pb = psi + (size_t)band * ldpsi;
-  zinv_tile<T, N>(m, chunk * ZS, sticks + (size_t)band * N * m.ldst, tw, L, [&](int s, int z) {
+  zinv_tile<N>(m, chunk * ZS, sticks + (size_t)band * N * m.ldst, tw, L, [&](int s, int z) {
     const int g = m.zidx[(size_t)z * m.nst + s];
-    return g >= 0 ? pw::to_t<T>(pb[g]) : cpx<T>{T(0), T(0)};
+    return g >= 0 ? pb[g] : c128{0.0, 0.0};
   });
 }
 
-template <typename T, int N>
+template <int N>
 __global__ void __launch_bounds__(zthreads<N>())
-k_zfwd_wave(SphereMap m, const cpx<T>* __restrict__ sticks, const c128* __restrict__ psi, int ldpsi,
-            c128* __restrict__ hpsi, int ldhpsi, const cpx<T>* __restrict__ tw, double inv_n, int accumulate, int gz,
+k_zfwd_wave(SphereMap m, const c128* __restrict__ sticks, const c128* __restrict__ psi, int ldpsi,
+            c128* __restrict__ hpsi, int ldhpsi, const c128* __restrict__ tw, double inv_n, int accumulate, int gz,
             int nb) {
-  __shared__ cpx<T> L[N * ZS];
+  __shared__ c128 L[N * ZS];
   int chunk, band;
   if (!pw::z_tile(gz, nb, chunk, band)) return;
   const c128* pb = psi + (size_t)band * ldpsi;
   c128* hb = hpsi + (size_t)band * ldhpsi;
-  zfwd_tile<T, N>(m, chunk * ZS, sticks + (size_t)band * N * m.ldst, tw, L, [&](int s, int z, cpx<T> v) {
+  zfwd_tile<N>(m, chunk * ZS, sticks + (size_t)band * N * m.ldst, tw, L, [&](int s, int z, c128 v) {
     const int g = m.zidx[(size_t)z * m.nst + s];
     if (g < 0) return;
-    c128 r = c128{(double)v.x * inv_n, (double)v.y * inv_n};
+    c128 r = c128{v.x * inv_n, v.y * inv_n};
     if (!(accumulate & 2)) {   // kinetic term (not yet in hpsi)
       const c128 p = pb[g];
       const double t = m.kin[g];
@@ -112,39 +112,39 @@ k_zfwd_wave(SphereMap m, const cpx<T>* __restrict__ sticks, const c128* __restri
   });
 }
 
-template <typename T, int N>
+template <int N>
 __global__ void __launch_bounds__(zthreads<N>())
-k_zinv_wave_g(SphereMap m, const c128* __restrict__ psi, int ldpsi, cpx<T>* __restrict__ sticks,
-              const cpx<T>* __restrict__ tw, int gz, int npair, int nbands) {
-  __shared__ cpx<T> L[N * ZS];
+k_zinv_wave_g(SphereMap m, const c128* __restrict__ psi, int ldpsi, c128* __restrict__ sticks,
+              const c128* __restrict__ tw, int gz, int npair, int nbands) {
+  __shared__ c128 L[N * ZS];
   int chunk, pair;
   if (!pw::z_tile(gz, npair, chunk, pair)) return;
   const c128* pa = psi + (size_t)(2 * pair) * ldpsi;
   const c128* pb = 2 * pair + 1 < nbands ? pa + ldpsi : nullptr;
-  zinv_tile<T, N>(m, chunk * ZS, sticks + (size_t)pair * N * m.ldst, tw, L, [&](int s, int z) {
+  zinv_tile<N>(m, chunk * ZS, sticks + (size_t)pair * N * m.ldst, tw, L, [&](int s, int z) {
     const int enc = m.zidx[(size_t)z * m.nst + s];
-    return enc >= 0 ? pw::to_t<T>(pw::gamma_pack(pa, pb, enc)) : cpx<T>{T(0), T(0)};
+    return enc >= 0 ? pw::gamma_pack(pa, pb, enc) : c128{0.0, 0.0};
   });
 }
 
 // in place: only the positions the gather reads are written back
-template <typename T, int N>
+template <int N>
 __global__ void __launch_bounds__(zthreads<N>())
-k_zfwd_wave_g(SphereMap m, cpx<T>* __restrict__ sticks, const cpx<T>* __restrict__ tw, int gz, int npair) {
-  __shared__ cpx<T> L[N * ZS];
+k_zfwd_wave_g(SphereMap m, c128* __restrict__ sticks, const c128* __restrict__ tw, int gz, int npair) {
+  __shared__ c128 L[N * ZS];
   int chunk, pair;
   if (!pw::z_tile(gz, npair, chunk, pair)) return;
-  cpx<T>* io = sticks + (size_t)pair * N * m.ldst;
-  zfwd_tile<T, N>(m, chunk * ZS, io, tw, L, [&](int s, int z, cpx<T> v) { io[(size_t)z * m.ldst + s] = v; });
+  c128* io = sticks + (size_t)pair * N * m.ldst;
+  zfwd_tile<N>(m, chunk * ZS, io, tw, L, [&](int s, int z, c128 v) { io[(size_t)z * m.ldst + s] = v; });
 }
 
 template <int N>
 pw::ZFns<double> entry() {
   pw::ZFns<double> f;
-  f.inv = k_zinv_wave<double, N>;
-  f.fwd = k_zfwd_wave<double, N>;
-  f.inv_g = k_zinv_wave_g<double, N>;
-  f.fwd_g = k_zfwd_wave_g<double, N>;
+  f.inv = k_zinv_wave<N>;
+  f.fwd = k_zfwd_wave<N>;
+  f.inv_g = k_zinv_wave_g<N>;
+  f.fwd_g = k_zfwd_wave_g<N>;
   f.sticks = ZS;
   f.threads = zthreads<N>();
   return f;
