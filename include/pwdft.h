@@ -93,9 +93,11 @@ typedef struct {
   int32_t      nb_max;       /* largest number of bands passed to hpsi_apply / davidson_solve      */
   int32_t      ndim_max;     /* largest Davidson basis factor (basis <= ndim*nb); 0 = no solver ws  */
   int32_t      plane_mode;   /* 0: the plane pass (y, x, V(r), x, y of one z plane) runs in one
-                                kernel per plane where the plane fits in LDS (the register form
-                                where two planes fit a workgroup, else the lane-group form, e.g.
-                                144^2 in both precisions), else in
+                                kernel per plane where the plane fits in LDS (in float64 the
+                                two-step form at 64^2 to 72^2; else the register form where two
+                                planes fit a workgroup, else the lane-group form, e.g. 144^2 in
+                                both precisions, else the two-step form in float64 where it covers
+                                the grid, else a generic kernel), else in
                                 three kernels through an HBM copy of the plane's x columns;
                                 1: always three kernels; 2: the lane-group form (16 lanes per 1D
                                 transform) wherever it applies (n1 = n2 in {80, 96, 128, 144},

@@ -2082,7 +2082,10 @@ bool nl_beside(pw_plan p, bool f64, int nb) {
              kPlaneRegMaxLds;
     default:
       // a two-step plane workgroup of 120^2 and more takes a CU's LDS and
-      // registers (256-atom Gamma block: 7.28 ms after, 7.84 beside)
+      // registers (256-atom Gamma block: 7.24 ms after, 7.69 beside).  Smaller
+      // planes stay beside, where part of a block gains (81^2: 50 bands 444
+      // against 469 us; 108^2: 100 bands 2.81 against 2.91 ms) what a whole one
+      // loses (200 bands 1682 against 1579 us; 400 bands 9.71 against 9.51 ms)
       return !(f64 && p->n2 >= 120 && plane_wave_of<double>(p->n1, p->n2, p->nxr).fn != nullptr);
   }
 }

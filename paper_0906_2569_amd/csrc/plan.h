@@ -84,7 +84,8 @@ struct pw_plan_s {
   int band_chunk = 0;       // bands per FFT pass (stick workspace capacity)
   bool split64 = false, split32 = false;  // three-kernel plane pass (float64 / float32)
   int form64 = 0, form32 = 0;   // plane pass form per precision: 0 register (quad) kernel,
-                                // 1 three kernels, 2 lane-group kernel, 3 generic LDS kernel
+                                // 1 three kernels, 2 lane-group kernel, 3 two-step kernel (float64)
+                                // or generic LDS kernel
   bool gamma = false;       // Gamma point: bands are real functions stored on the half sphere (npw
                             // entries, G = 0 first); the transforms cover the whole sphere (nfull)
   int nfull = 0;

@@ -32,8 +32,18 @@ constexpr int plane_wave_points(int n1, int n2) {
 }
 constexpr int plane_wave_threads(int n1, int n2) { return plane_wave_points(n1, n2) <= 10 ? 768 : 512; }
 
-// (see twiddle_powers)
-constexpr bool hold_twiddles(int points) { return points != 10 && points < 25; }
+// Twiddle factors of an axis.  Held is faster (120^2 Gamma block 7.20 against
+// 7.33 ms) except in steps whose kernels have no registers left: of 10 points
+// at three waves per SIMD (50^2 block 112 us held, 100 read again) and of 25
+// (125^2 778 and 704 us).  Three held cost up to 9% in the same way (81^2 199
+// and 218 us), and are taken on the lengths where two round more than the table
+// kernels (V psi on 25^3 1.15 against 1.04 times them, 64^3 1.05 and 1.00, 27^3
+// 1.05 and 0.98).
+template <class X>
+constexpr wavefft::Twiddles twiddles_of() {
+  if (X::A == 10 || X::A >= 25) return wavefft::kAgain;
+  return X::N == 25 || X::N == 27 || X::N == 64 ? wavefft::kThree : wavefft::kTwo;
+}
 
 // The planes of one workgroup in LDS: each plane's x columns [nxr][ys], a column of
 // zeros (read where the sphere has no column) and one that takes what is
@@ -75,7 +85,7 @@ __device__ __forceinline__ void inverse_y(const SphereMap& m, const BufView& st,
 #pragma unroll
       for (int j = 0; j < Yx::A; ++j) x[r][j] = Yx::used(j) ? st.load(s[j]) : c128{0.0, 0.0};
       wavefft::WDft<Yx::A>::run(x[r], 1.0);
-      wavefft::twiddle_powers<Yx::A, hold_twiddles(Yx::A)>(x[r], tw2, b, false);
+      wavefft::twiddle_powers<Yx::A, twiddles_of<Yx>()>(x[r], tw2, b, false);
     }
     wavefft::exchange_ab<Yx>(x, y, W, lane);
 #pragma unroll
@@ -118,7 +128,7 @@ __device__ __forceinline__ void inverse_x_first(const c128* Y, const PlaneLds& L
 #pragma unroll
     for (int j = 0; j < X::A; ++j) x[r][j] = X::used(j) ? yp[off[r][j]] : c128{0.0, 0.0};
     wavefft::WDft<X::A>::run(x[r], 1.0);
-    wavefft::twiddle_powers<X::A, hold_twiddles(X::A)>(x[r], tw1, b, false);
+    wavefft::twiddle_powers<X::A, twiddles_of<X>()>(x[r], tw1, b, false);
   }
 }
 
@@ -172,7 +182,7 @@ k_plane_wave(SphereMap m, c128* __restrict__ sticks, const double* __restrict__ 
 #pragma unroll
     for (int r = 0; r < X::R1; ++r) {
       const int id = lane + 64 * r, b = id % X::B, row = q0 + id / X::B;
-      wavefft::twiddle_powers<X::A, hold_twiddles(X::A)>(x[r], tw1, b, true);
+      wavefft::twiddle_powers<X::A, twiddles_of<X>()>(x[r], tw1, b, true);
       wavefft::WDft<X::A>::run(x[r], -1.0);
       if (id < X::RB * X::B && row < nrow) {
         const int pz = row / N2;
@@ -200,7 +210,7 @@ k_plane_wave(SphereMap m, c128* __restrict__ sticks, const double* __restrict__ 
 #pragma unroll
     for (int r = 0; r < Yx::R1; ++r) {
       const int id = lane + 64 * r, b = id % Yx::B, c = c0 + id / Yx::B;
-      wavefft::twiddle_powers<Yx::A, hold_twiddles(Yx::A)>(x[r], tw2, b, true);
+      wavefft::twiddle_powers<Yx::A, twiddles_of<Yx>()>(x[r], tw2, b, true);
       wavefft::WDft<Yx::A>::run(x[r], -1.0);
       int s[Yx::A];
       sticks_of<Yx>(m, min(c, ncol - 1), id < Yx::RB * Yx::B && c < ncol, b, s);

@@ -177,33 +177,30 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// x[k] *= w^k, k < A, w = tw[b] (conjugated where `conj`): w, w^4 and where
-// registers allow w^2 from the table, the other powers as products of those, so
-// that no power is far from the table.  (In one chain of w^2, A / 2 deep, the
-// rounding of V psi was 1.14 to 1.97 times that of the three-kernel plane pass,
-// which reads every power: now 0.82 to 1.02 times on 50^2 to 120^2.)
-//
-// HOLD: w and w^4 stay in registers over the passes of a caller's loop, and the
-// compiler is kept from computing all powers ahead of it (2 A registers, spilled);
-// else the three are read again in each pass.  Held is faster (120^2 Gamma block
-// 7.20 against 7.33 ms) except in steps whose kernels have no registers left: of 10
-// points at three waves per SIMD (50^2 block 112 us held, 100 read again) and of
-// 25 (125^2, 778 and 704).
-template <int A, bool HOLD>
+// How twiddle_powers takes its factors: w and w^4 (kTwo) or w, w^2 and w^4
+// (kThree) held in registers over the passes of a caller's loop, the compiler
+// kept from computing all powers ahead of it (2 A registers, spilled); or the
+// three read again in each pass (kAgain).
+enum Twiddles { kTwo, kThree, kAgain };
+
+// x[k] *= w^k, k < A, w = tw[b] (conjugated where `conj`): two or three powers
+// from the table, the others as products of those, so that none is far from the
+// table.  (In one chain of w^2, A / 2 deep, the rounding of V psi was up to
+// twice that of the kernels that read every power: 75^3 2.2, 120^3 1.44, 50^3
+// 1.34 times; now 0.7 to 1.04 times on 25^3 to 120^3.)
+template <int A, Twiddles HOW>
 __device__ __forceinline__ void twiddle_powers(c128 (&x)[A], const c128* __restrict__ tw, int b, bool conj) {
   auto get = [&](int i) {
     c128 w = tw[i];
     if (conj) w.y = -w.y;
     return w;
   };
-  if constexpr (!HOLD) asm volatile("" : "+v"(b));
-  c128 w1 = get(b), w4 = get(4 * b), w2;
-  if constexpr (HOLD) {
-    asm volatile("" : "+v"(w1.x), "+v"(w1.y), "+v"(w4.x), "+v"(w4.y));
-    w2 = cmul(w1, w1);
-  } else {
-    w2 = get(2 * b);
-  }
+  if constexpr (HOW == kAgain) asm volatile("" : "+v"(b));
+  c128 w1 = get(b), w4 = get(4 * b), w2{0.0, 0.0};
+  if constexpr (HOW != kTwo) w2 = get(2 * b);
+  if constexpr (HOW != kAgain) asm volatile("" : "+v"(w1.x), "+v"(w1.y), "+v"(w4.x), "+v"(w4.y));
+  if constexpr (HOW == kThree) asm volatile("" : "+v"(w2.x), "+v"(w2.y));
+  if constexpr (HOW == kTwo) w2 = cmul(w1, w1);
   const c128 w3 = cmul(w1, w2);
   x[1] = cmul(x[1], w1);
   x[2] = cmul(x[2], w2);

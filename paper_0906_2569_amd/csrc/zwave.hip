@@ -29,7 +29,7 @@ __device__ __forceinline__ void zinv_tile(const SphereMap& m, int s0, c128* __re
 #pragma unroll
     for (int j = 0; j < X::A; ++j) x[j] = (X::used(j) && s < m.nst) ? load(s, u + X::B * j) : c128{0.0, 0.0};
     wavefft::WDft<X::A>::run(x, 1.0);
-    wavefft::twiddle_powers<X::A, false>(x, tw, u, false);
+    wavefft::twiddle_powers<X::A, wavefft::kAgain>(x, tw, u, false);
 #pragma unroll
     for (int k = 0; k < X::A; ++k) L[(k * X::B + u) * ZS + sl] = x[k];
   }
@@ -63,7 +63,7 @@ __device__ __forceinline__ void zfwd_tile(const SphereMap& m, int s0, const c128
     c128 x[X::A];
 #pragma unroll
     for (int k = 0; k < X::A; ++k) x[k] = L[(k * X::B + u) * ZS + sl];
-    wavefft::twiddle_powers<X::A, false>(x, tw, u, true);
+    wavefft::twiddle_powers<X::A, wavefft::kAgain>(x, tw, u, true);
     wavefft::WDft<X::A>::run(x, -1.0);
 #pragma unroll
     for (int j = 0; j < X::A; ++j)
