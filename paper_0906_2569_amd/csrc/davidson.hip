@@ -433,10 +433,10 @@ constexpr double kSub32MinFlops = 1e11;
 // plain reduction (1e-9 to 1e-6 Ha in nearly dependent bases) is within reach,
 // and what a solve returns follows every rounding before it: a caller of the
 // default limit gets the bits this arithmetic has always given (8 atoms, 16
-// bands, tolerance 1e-10: 57 of 100 starts converge in 45 to 167 iterations,
-// the rest run to 200 or break down, with a density up to 6e-8 off).  A lower
-// limit does not leave it those iterations, and takes the Hermitian mean (43
-// to 76 iterations in all 100 starts; density within 5e-11).
+// bands, tolerance 1e-10: 34 of 60 starts converge, in 45 to 167 iterations, 23
+// run to 200 with a density up to 1.4e-7 off, 3 met a second singular overlap).
+// A lower limit does not leave it those iterations, and takes the Hermitian mean
+// (43 to 76 iterations in 100 of 100 starts; density within 1.3e-10).
 constexpr double kPlainTol = 1e-8;
 constexpr int kPlainIters = 200;
 

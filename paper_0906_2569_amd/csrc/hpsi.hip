@@ -1119,7 +1119,8 @@ bool plane_form_ok(int form, int n1, int n2, int nxr, bool plain = false) {
 // applies; 0 (and 3, before its measurement, and 2 and 4 elsewhere) the
 // register (quad) kernel where two planes fit a workgroup, else the
 // lane-group kernel, else the register kernel with one plane per workgroup,
-// else the generic LDS kernel, else three kernels.  (At 144^2 in float32 the
+// else the LDS form (two-step kernel in float64 where one covers the grid, or
+// generic kernel), else three kernels.  (At 144^2 in float32 the
 // lane-group kernel runs two workgroups per CU where the one-plane register
 // kernel runs one: 12.5 against 18.4 ms per 1024-band H.psi.)  plain: without
 // the two-step kernels.

@@ -1331,7 +1331,7 @@ __global__ void __launch_bounds__(NT) k_tridiag_coop(int n, c128* __restrict__ A
 // bound by that latency chain (1.1 us a column at 48 rows, 1.5 at 80, 2.5 for the
 // first of 96, where the float64 FMAs of one CU, 12 per entry, add to it).  48 rows 308 -> 56 us and
 // 63 rows 400 -> 82 against k_tridiag, which goes through memory; 64 rows 239
-// -> 79 and 96 rows 385 -> 160 against the cooperative kernel (3.7 us a column).
+// -> 79 and 96 rows 385 -> 165 against the cooperative kernel (3.7 us a column).
 // At 128 rows the entries spill (558 us against 486): larger blocks hand
 // over at 96.
 // ---------------------------------------------------------------------------
@@ -1480,7 +1480,7 @@ void tridiag_reg(int n, int base, bool pending, c128* A, int ld, double* d, doub
     kernel<<<1, threads, 0, st>>>(n, base, pending ? 1 : 0, stop, A, ld, d, e, tau, info);
   };
   // One wave per SIMD up to 80 rows (their chain is bound by issue).  96 rows
-  // need two for the registers: 181 us alone, 155 if the last 80 rows, 117 us,
+  // need two for the registers: 181 us alone, 165 if the last 80 rows, 120 us,
   // are left to the kernel of one wave
   if (n - base > 80) {
     const int stop = n - base - 80;
