@@ -1059,7 +1059,6 @@ __global__ void __launch_bounds__(NT) k_tridiag_coop(int n, c128* __restrict__ A
   for (int c = 0; c < NC; ++c) {
     jc[c] = (tid % CBW) + CBW * c;
     ok[c] = jc[c] < n;
-    // (one copy of the columns, the first row group's, writes the own rows)
     own[c] = half == 0 && ok[c] ? local_of(jc[c]) : -1;
   }
 
@@ -1078,11 +1077,23 @@ __global__ void __launch_bounds__(NT) k_tridiag_coop(int n, c128* __restrict__ A
   if (tid < CRT) { s_rv[0][tid] = s_rv[1][tid] = s_rw[tid] = c128{0.0, 0.0}; }
   __syncthreads();
 
-  // own-row values of a column vector to LDS
+  // own-row values of a column vector to LDS (one copy: the first row group
+  // writes).  With several columns a thread the compiler contracts the updates
+  // above into other fused products where the index is kept, and an eigenvector's
+  // sign follows that rounding: there the bare solver's forms find it anew.
   auto put_own = [&](c128* dst, const c128 (&val)[NC]) {
+    if constexpr (NC == 1 || FAST) {
 #pragma unroll
-    for (int c = 0; c < NC; ++c)
-      if (own[c] >= 0) dst[own[c]] = val[c];
+      for (int c = 0; c < NC; ++c)
+        if (own[c] >= 0) dst[own[c]] = val[c];
+    } else {
+      if (half != 0) return;
+#pragma unroll
+      for (int c = 0; c < NC; ++c) {
+        const int li = local_of(jc[c]);
+        if (li >= 0 && ok[c]) dst[li] = val[c];
+      }
+    }
   };
   // y = B v on the own rows: per-thread partial sums, then per-wave totals to s_red
   auto rows_times = [&](const c128 (&acc)[RH]) {
